@@ -103,7 +103,12 @@ typedef struct {
                                    NULL = nt_max for every shot                  */
 } fwi_geometry;
 
-/* Execution settings (all fields 0 = automatic). */
+/* Execution settings (all fields 0 = automatic).  Where a launch of the z
+ * sweeps (one wavefront walking a tile's rows) would not fill the GPU, sweeps
+ * whose fields below are 0 (tile rows, prefetch, steps per launch) hold their
+ * tiles in LDS and run several time steps per launch, outside graphs; the
+ * results have the same bits as the one-step z sweeps'.  Naming one of those
+ * fields selects the z sweep it belongs to. */
 typedef struct {
     int32_t mode;             /* FWI_EXEC_BATCHED (default) or FWI_EXEC_PLAIN:
                                  plain = one shot at a time, one launch per
@@ -268,7 +273,8 @@ int fwi_gradient_static(const fwi_grid *grid, const fwi_geometry *geom, const fw
  * dJ/dv; image is [2*hmax+1][nz][nx] float, 0 <= hmax <= 32, hmax < nx.
  * Workspace: fwi_workspace_bytes(..., FWI_WS_EXTIMAGE, hmax); besides the
  * gradient's buffers it holds lam and D of the model cells for graph_steps
- * reverse steps per shot in flight (32 in plain mode). */
+ * reverse steps per shot in flight (32 in plain mode and for the
+ * LDS-resident sweeps). */
 int fwi_extended_image(const fwi_grid *grid, const fwi_geometry *geom, const fwi_exec *exec,
                        const float *v, const float *wavelet, int64_t wavelet_stride,
                        const float *d_obs, int misfit, double *J, float *grad,

@@ -6,7 +6,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libfwi.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("fwi_kernels.hip", "fwi_dft.hip", "fwi_runtime.hip")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("fwi_kernels.hip", "fwi_block.hip", "fwi_dft.hip",
+                                                             "fwi_runtime.hip")]
 ARCH = os.environ.get("FWI_OFFLOAD_ARCH", "gfx950")
 
 

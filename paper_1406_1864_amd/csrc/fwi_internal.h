@@ -177,6 +177,29 @@ struct EpiArgs {
   const int32_t* err;
 };
 
+// LDS-resident tiles, several time steps per launch (fwi_block.hip): region
+// shapes RX x RZ, by the rows of a thread's patch: one row (512 threads for
+// 32 rows, 1024 for 64), two (512) or four (256).  At most kBlkRecv receivers
+// per shot and kBlkSponge sponge cells (what their LDS tables hold).
+enum : int { kBlkSmall = 0, kBlkWide = 1, kBlkPair = 2, kBlkTall = 3 };
+constexpr int kBlkRX[] = {64, 64, 64, 64};
+constexpr int kBlkRZ[] = {32, 64, 64, 64};
+constexpr int kBlkRecv = 1024;
+constexpr int kBlkSponge = 128;
+constexpr int kBlkSteps = 256;  // time steps of one launch at most
+struct BlockArgs {
+  StepArgs s;           // step = launch index: launch q runs steps q T .. q T + T - 1
+  int32_t shape;        // kBlkSmall .. kBlkTall
+  int32_t T;            // time steps per launch
+  int32_t nbx, nbz;     // tiles along x and z
+  int32_t sx, sz;       // distance of neighbouring regions (sx a multiple of 4)
+  int32_t c0;           // first region's storage column (a multiple of 4)
+  const int2* rcell;    // [ntrace] (padded row, storage column) of each receiver
+  int64_t bstride;      // floats per checkpoint set of the Born field
+};
+hipError_t launch_forward_block(const BlockArgs& a, int flags, hipStream_t s);
+hipError_t launch_reverse_block(const BlockArgs& a, int flags, hipStream_t s);
+
 // host-side launchers (fwi_kernels.hip)
 hipError_t launch_prep(const Dims& d, const float* v, float* w, double dt, double h, float vmax,
                        int32_t* err, hipStream_t s);
@@ -195,10 +218,11 @@ hipError_t launch_ext_image(const ExtArgs& a, hipStream_t s);
 // free surface
 hipError_t launch_reverse2(const StepArgs& a, int prefetch, int flags, hipStream_t s);
 hipError_t launch_forward2(const StepArgs& a, int prefetch, hipStream_t s);
-// after a two-step forward sweep: shots whose final state sits in the second
-// set of u levels (an odd number of launches) get it copied to the first
+// after a forward sweep of spl steps per launch: shots whose final state sits
+// in the second set of u levels (an odd number of launches) get it copied to
+// the first
 hipError_t launch_forward2_finish(float* u, int64_t ustride, int64_t set_floats, const SlotInfo* slots,
-                                  const ShotDesc* shots, int S, hipStream_t s);
+                                  const ShotDesc* shots, int S, int spl, hipStream_t s);
 hipError_t launch_ext_out(const Dims& d, const float* Iacc, int groups, int hmax, const float* v, float* image,
                           const int32_t* err, hipStream_t s);
 hipError_t launch_advance(int32_t* ctr, int32_t by, hipStream_t s);

@@ -1736,13 +1736,13 @@ hipError_t launch_forward2(const StepArgs& a, int prefetch, hipStream_t s) {
   return hipGetLastError();
 }
 
-// one block row per slot: a shot of nt samples ran nt/2 two-step launches
-// (rounded down: ceil((nt-1)/2)); with an odd count its state is in set 1
+// one block row per slot: a shot of nt samples ran ceil((nt-1)/spl) launches;
+// with an odd count its state is in set 1
 __global__ void k_forward2_finish(float* u, int64_t ustride, int64_t set_floats, const SlotInfo* slots,
-                                  const ShotDesc* shots) {
+                                  const ShotDesc* shots, int spl) {
   const SlotInfo si = slots[blockIdx.y];
   if (si.shot < 0) return;
-  if (((shots[si.shot].nt / 2) & 1) == 0) return;
+  if ((((shots[si.shot].nt + spl - 2) / spl) & 1) == 0) return;
   float* base = u + (int64_t)si.cs * ustride;
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < set_floats;
        k += (int64_t)gridDim.x * blockDim.x)
@@ -1750,10 +1750,11 @@ __global__ void k_forward2_finish(float* u, int64_t ustride, int64_t set_floats,
 }
 
 hipError_t launch_forward2_finish(float* u, int64_t ustride, int64_t set_floats, const SlotInfo* slots,
-                                  const ShotDesc* shots, int S, hipStream_t s) {
+                                  const ShotDesc* shots, int S, int spl, hipStream_t s) {
   if (S <= 0 || set_floats <= 0) return hipSuccess;
   const unsigned bx = (unsigned)std::min<int64_t>((set_floats + 255) / 256, 1024);
-  hipLaunchKernelGGL(k_forward2_finish, dim3(bx, S), dim3(256), 0, s, u, ustride, set_floats, slots, shots);
+  hipLaunchKernelGGL(k_forward2_finish, dim3(bx, S), dim3(256), 0, s, u, ustride, set_floats, slots, shots,
+                     spl);
   return hipGetLastError();
 }
 

@@ -124,7 +124,12 @@ enum Phase { kPhaseFwd = 0, kPhaseRev = 1 };
 
 struct Layout {
   size_t hdr, shots, slots, rdir, rrows, rmaps, trace_shot;
-  size_t w, traces, jpart, u, lam, g, E, snap, strip, xlam, xD, xI, bu, bw, rslots, rdir2, rrows2, rmaps2, total;
+  size_t w, traces, jpart, u, lam, g, E, snap, strip, xlam, xD, xI, bu, bw, rslots, rdir2, rrows2, rmaps2, rcell, total;
+};
+
+// tiling of the LDS-resident sweeps (fwi_block.hip); T = 0: z sweeps
+struct BlkPlan {
+  int shape = 0, T = 0, nbx = 0, nbz = 0, sx = 0, sz = 0, c0 = 0;
 };
 
 // device header at the start of every workspace
@@ -151,7 +156,8 @@ struct Plan {
   int rev_steps = 1;           // time steps per launch of the plain reverse sweep (1 or 2)
   int fwd_steps = 1;           // time steps per launch of the gradient's forward sweep (1 or 2)
   int branches = 1;            // independent chains per captured chunk of a two-step sweep
-  int ulevels = kULevels, llevels = kLamLevels;
+  BlkPlan bf, br;              // LDS-resident forward / reverse sweeps (T = 0: off)
+  int ulevels = kULevels, llevels = kLamLevels, blevels = kULevels;
   int XT2 = 0;                 // tiles of the two-step reverse sweep along x
   double sp_a = 0.0;
   double dx = 0, dt = 0;
@@ -170,6 +176,7 @@ struct Plan {
   std::vector<RmapRow> rrows2;
   std::vector<int32_t> rmaps2;
   std::vector<int32_t> trace_shot;
+  std::vector<int2> rcell;     // (padded row, storage column) of every receiver
   int64_t snap_stride = 0, strip_stride = 0;
   Layout L{};
   std::map<std::vector<uint64_t>, hipGraphExec_t> graphs;
@@ -188,6 +195,7 @@ struct Plan {
 struct ExecChoice {
   int S, TZ, graph_steps, pf_fwd, pf_rev, Sr, TZr, rsteps, fsteps;
   int branches = 0;  // independent chains per captured two-step chunk (0: kDefaultBranches)
+  int blk = 0;       // LDS-resident sweeps where blk_tiling() has one: 1 forward, 2 reverse
 };
 
 std::mutex g_mutex;
@@ -269,6 +277,65 @@ void build_dims(Plan& p, const fwi_grid* g, int TZ) {
   d.model = (int64_t)d.nz * d.nx;
 }
 
+// The tiling of the LDS-resident sweeps for `runs` shots in flight, or none.
+bool blk_fit(const Dims& d, int shape, int T, BlkPlan& b) {
+  const int RX = kBlkRX[shape], RZ = kBlkRZ[shape];
+  b = BlkPlan{};
+  b.shape = shape;
+  b.T = T;
+  b.c0 = d.off & ~3;
+  const int W = d.off + d.X - b.c0, R = d.Z - d.ztop;
+  const int SX = RX - 2 * kRadius * T, SZ = RZ - 2 * kRadius * T;
+  auto cut = [](int n, int region, int stride, int& nb, int& step, int unit) {
+    nb = 1;
+    step = 0;
+    if (n <= region) return true;
+    if (stride < unit) return false;
+    nb = (n - region + stride - 1) / stride + 1;
+    step = (n - region + nb - 2) / (nb - 1);
+    step = (step + unit - 1) / unit * unit;
+    return true;
+  };
+  return cut(W, RX, SX, b.nbx, b.sx, 4) && cut(R, RZ, SZ, b.nbz, b.sz, 1);
+}
+
+// Which sweeps run LDS-resident, from the cells of one step (runs * Z * X) and
+// the tiles they make.  Measured per time step against the two-step z sweeps
+// at their best tile rows (us, LDS-resident / z sweep):
+//   cells        0.04 M     0.15 M     0.55 M     2.0 M      3.9 M      7.8 M
+//   forward    3.2 / 12.2 3.8 / 13.4 5.0 / 13.9 11.0 / 16.4 15.5 / 19.4 25.4 / 25.2
+//   reverse    3.7 / 12.2 4.3 / 13.1 7.5 / 13.7 20.1 / 18.8 32.5 / 28.9 67.6 / 47.0
+// The z sweeps' floor is their rows' latency; past the lines below they move
+// fewer bytes and repeat less work at the tiles' margins.
+constexpr int64_t kBlkFwdCells = 8000000, kBlkRevCells = 2200000;
+constexpr int kBlkCUs = 256;
+
+// chunked: launches end at every 32nd step (windows of captured series or of
+// the extended image), so T divides 32.
+BlkPlan blk_tiling(const Dims& d, int runs, bool rev, bool born, bool chunked) {
+  BlkPlan b;
+  if (d.N > kBlkSponge) return b;
+  if ((int64_t)runs * d.Z * d.X > (rev ? kBlkRevCells : kBlkFwdCells)) return b;
+  const int W = d.off + d.X - (d.off & ~3), R = d.Z - d.ztop;
+  // one tile: the whole record in a few launches
+  for (int shape : {kBlkSmall, kBlkWide})
+    if (W <= kBlkRX[shape] && R <= kBlkRZ[shape]) return blk_fit(d, shape, chunked ? 32 : kBlkSteps, b) ? b : BlkPlan{};
+  // The fewer the tiles, the more steps pay for a launch (its fixed part is 6
+  // to 8 us) and the more wavefronts a tile needs to run fast by itself
+  // (kBlkWide: 16); with several tiles per CU smaller workgroups fill it
+  // better, and a forward tile of 4 rows per thread (kBlkTall) reads least.
+  auto tiles = [&](int T) {
+    BlkPlan t;
+    return blk_fit(d, kBlkWide, T, t) ? (int64_t)t.nbx * t.nbz * runs : INT64_MAX;
+  };
+  if (!chunked && tiles(6) <= kBlkCUs) return blk_fit(d, kBlkWide, 6, b) ? b : BlkPlan{};
+  const int64_t t4 = tiles(4);
+  if (t4 <= kBlkCUs && (rev || born)) return blk_fit(d, kBlkWide, 4, b) ? b : BlkPlan{};
+  if (born) return blk_fit(d, kBlkTall, chunked ? 2 : 3, b) ? b : BlkPlan{};
+  if (rev || t4 <= 4 * kBlkCUs) return blk_fit(d, kBlkPair, 4, b) ? b : BlkPlan{};
+  return blk_fit(d, kBlkTall, chunked ? 2 : 3, b) ? b : BlkPlan{};
+}
+
 // what: FWI_WS_FORWARD / GRADIENT / HESSIAN / AUTOGRAD / EXTIMAGE; ext_h: offset
 // bound of the extended image (EXTIMAGE only; -1 leaves its buffers out)
 std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, const ExecChoice& ex,
@@ -306,6 +373,19 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   p->branches = ex.branches > 0 ? ex.branches : kDefaultBranches;
   p->ulevels = fwd2 ? 2 * kULevels : (rev2 ? kULevels2 : kULevels);
   p->llevels = rev2 ? kLamLevels2 : kLamLevels;
+  const bool grad = (what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE ||
+                     what == FWI_WS_GNHVP);
+  int most_recv = 0;
+  for (int s = 0; s < geo->nshot; ++s) most_recv = std::max(most_recv, geo->rec_ptr[s + 1] - geo->rec_ptr[s]);
+  if (!plain && most_recv <= kBlkRecv) {
+    const bool chunked = what == FWI_WS_EXTIMAGE || ex.graph_steps == 0;  // steps counted in windows of 32
+    if ((ex.blk & 1) && !fwd2) p->bf = blk_tiling(d, p->S, false, what == FWI_WS_BORN || what == FWI_WS_GNHVP, chunked);
+    if ((ex.blk & 2) && grad && !rev2) p->br = blk_tiling(d, p->Sr, true, false, chunked);
+    // two sets of levels: neighbouring tiles read each other's inputs
+    if (p->bf.T || p->br.T) p->ulevels = std::max(p->ulevels, 2 * kULevels);
+    if (p->br.T) p->llevels = kLamLevels2;
+    if (p->bf.T) p->blevels = 2 * kULevels;
+  }
   p->XT2 = kWavesPerBlock * ((d.X + kBlk2 - 1) / kBlk2);
   const double eta_max = 3.0 * g->v_ref * std::log(1e3) / (2.0 * d.N * g->dx);
   p->sp_a = 0.5 * g->dt * eta_max / ((double)d.N * d.N);
@@ -313,6 +393,8 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   const int ns = geo->nshot;
   p->ntrace = ns > 0 ? geo->rec_ptr[ns] : 0;
   p->trace_shot.assign(std::max(p->ntrace, 1), 0);
+  p->rcell.assign(std::max(p->ntrace, 1), make_int2(0, 0));
+  for (int r = 0; r < p->ntrace; ++r) p->rcell[r] = make_int2(geo->rec_iz[r] + d.N, geo->rec_ix[r] + d.mx0);
   p->shots.resize(std::max(ns, 1));
   int max_nsnap = 0;
   for (int s = 0; s < ns; ++s) {
@@ -438,15 +520,13 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   if (p->rslots.empty()) p->rslots.assign(p->Sr, SlotInfo{-1, 0});
 
   // workspace layout
-  const bool grad = (what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE ||
-                     what == FWI_WS_GNHVP);
   const bool hess = (what == FWI_WS_HESSIAN);
   p->born = (what == FWI_WS_BORN || what == FWI_WS_GNHVP) ? 1 : 0;
   const bool ext = (what == FWI_WS_EXTIMAGE && ext_h >= 0);
   p->ext_h = ext ? ext_h : -1;
   // the ring holds the reverse steps of one graph chunk (two per launch for
   // the two-step sweep)
-  p->ext_T = ext ? (p->graph_steps > 0 ? p->graph_steps : 32) * p->rev_steps : 0;
+  p->ext_T = ext ? (p->graph_steps > 0 && !p->br.T ? p->graph_steps : 32) * p->rev_steps : 0;
   Layout& L = p->L;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -465,6 +545,7 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   L.rrows2 = take(sizeof(RmapRow) * p->rrows2.size());
   L.rmaps2 = take(sizeof(int32_t) * p->rmaps2.size());
   L.trace_shot = take(sizeof(int32_t) * p->trace_shot.size());
+  L.rcell = take(sizeof(int2) * p->rcell.size());
   L.w = take(sizeof(float) * d.field);
   L.traces = take(sizeof(float) * (size_t)g->nt_max * std::max(p->ntrace, 1));
   L.jpart = take(sizeof(double) * std::max(p->ntrace, 1));
@@ -483,7 +564,7 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   // up to 4 slot groups fold in parallel for |h| <= 16 (one for larger offsets)
   p->ext_groups = ext ? (p->ext_h <= 16 ? std::min(p->Sr, 4) : 1) : 1;
   L.xI = ext ? take(sizeof(float) * d.model * (2 * p->ext_h + 1) * p->ext_groups) : o;
-  L.bu = p->born ? take(sizeof(float) * (kULevels * d.field * p->ncs + d.guard)) : o;
+  L.bu = p->born ? take(sizeof(float) * (p->blevels * d.field * p->ncs + d.guard)) : o;
   L.bw = p->born ? take(sizeof(float) * d.field) : o;
   L.total = o;
   return p;
@@ -533,6 +614,21 @@ StepArgs step_args(const Plan& p, void* ws, int batch, int phase, const float* w
   a.bu = p.born ? at<float>(ws, p.L.bu) + p.d.guard : nullptr;
   a.bw = p.born ? at<float>(ws, p.L.bw) : nullptr;
   return a;
+}
+
+BlockArgs block_args(const Plan& p, void* ws, const StepArgs& a, const BlkPlan& b) {
+  BlockArgs o{};
+  o.s = a;
+  o.shape = b.shape;
+  o.T = b.T;
+  o.nbx = b.nbx;
+  o.nbz = b.nbz;
+  o.sx = b.sx;
+  o.sz = b.sz;
+  o.c0 = b.c0;
+  o.rcell = at<int2>(ws, p.L.rcell);
+  o.bstride = (int64_t)p.blevels * p.d.field;
+  return o;
 }
 
 ExtArgs ext_args(const Plan& p, void* ws, int rbatch) {
@@ -604,6 +700,25 @@ StepArgs slot_range(const StepArgs& a, int s0, int n) {
 int run_steps(Plan& p, void* ws, int batch, int phase, int flags, int nsteps, const float* wavelet,
               int64_t wstride, hipStream_t stream) {
   if (nsteps <= 0) return FWI_OK;
+  const BlkPlan& blk = phase == kPhaseFwd ? p.bf : p.br;
+  if (blk.T > 0) {
+    // LDS-resident sweep: T steps per launch, direct launches
+    BlockArgs a = block_args(p, ws, step_args(p, ws, batch, phase, wavelet, wstride), blk);
+    const bool fold = phase == kPhaseRev && (flags & kRevExt);
+    if (fold && (p.ext_h < 0 || p.ext_T % blk.T)) return fail(FWI_ERR_STATE, "extended image without its buffers");
+    for (int k = 0; k * blk.T < nsteps; ++k) {
+      a.s.step = k;
+      HIP_TRY(phase == kPhaseFwd ? launch_forward_block(a, flags, stream) : launch_reverse_block(a, flags, stream));
+      const int done = std::min((k + 1) * blk.T, nsteps);
+      if (fold && (done % p.ext_T == 0 || done == nsteps)) {
+        ExtArgs e = ext_args(p, ws, batch);
+        e.step0 = (done - 1) - (done - 1) % p.ext_T;
+        e.count = done - e.step0;
+        HIP_TRY(launch_ext_image(e, stream));
+      }
+    }
+    return FWI_OK;
+  }
   // the plain reverse sweep of a two-step plan, or the gradient's forward
   // sweep of one: launches of two steps each
   const bool two_rev = phase == kPhaseRev && (flags & ~kRevExt) == 0 && p.rev_steps == 2;
@@ -760,6 +875,8 @@ int upload_tables(const Plan& p, void* ws, hipStream_t s) {
                          hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(at<char>(ws, p.L.rmaps2), p.rmaps2.data(), sizeof(int32_t) * p.rmaps2.size(),
                          hipMemcpyHostToDevice, s));
+  HIP_TRY(hipMemcpyAsync(at<char>(ws, p.L.rcell), p.rcell.data(), sizeof(int2) * p.rcell.size(),
+                         hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(at<char>(ws, p.L.trace_shot), p.trace_shot.data(),
                          sizeof(int32_t) * p.trace_shot.size(), hipMemcpyHostToDevice, s));
   return FWI_OK;
@@ -784,12 +901,14 @@ int forward_batch(Plan& p, void* ws, int b, int flags, const float* wavelet, int
   HIP_TRY(launch_fill_slots(at<float>(ws, p.L.u), p.ulevels * p.d.field, p.ulevels * p.d.field + p.d.guard, slots,
                             p.S, 1, s));
   if (flags & kFwdBorn)
-    HIP_TRY(launch_fill_slots(at<float>(ws, p.L.bu), kULevels * p.d.field, kULevels * p.d.field + p.d.guard, slots,
+    HIP_TRY(launch_fill_slots(at<float>(ws, p.L.bu), p.blevels * p.d.field, p.blevels * p.d.field + p.d.guard, slots,
                               p.S, 1, s));
   if (int rc = run_steps(p, ws, b, kPhaseFwd, flags, p.batch_nt[b] - 1, wavelet, wstride, s)) return rc;
-  if (flags == (kFwdRecord | kFwdCkpt) && p.fwd_steps == 2)
+  // the reverse sweep starts from the first set of levels
+  const int spl = p.bf.T ? p.bf.T : (flags == (kFwdRecord | kFwdCkpt) ? p.fwd_steps : 1);
+  if ((flags & kFwdCkpt) && spl > 1)
     HIP_TRY(launch_forward2_finish(at<float>(ws, p.L.u) + p.d.guard, p.ulevels * p.d.field, kULevels * p.d.field,
-                                   slots, at<ShotDesc>(ws, p.L.shots), p.S, s));
+                                   slots, at<ShotDesc>(ws, p.L.shots), p.S, spl, s));
   return FWI_OK;
 }
 
@@ -1063,6 +1182,17 @@ struct CallCtx {
   std::shared_ptr<Plan> plan;
 };
 
+// The LDS-resident sweeps stand in for the z sweeps unless the caller sets
+// what only the z sweeps have: rows per tile, prefetch, steps per launch.
+int blk_allowed(const fwi_exec* ex) {
+  if (!ex) return 3;
+  if (ex->mode == FWI_EXEC_PLAIN) return 0;
+  int blk = 3;
+  if (ex->tile_rows > 0 || ex->prefetch > 0 || ex->forward_steps > 0) blk &= ~1;
+  if (ex->tile_rows > 0 || ex->tile_rows_reverse > 0 || ex->prefetch_reverse > 0 || ex->reverse_steps > 0) blk &= ~2;
+  return blk;
+}
+
 ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex) {
   ExecChoice c{};
   const int Z = g->nz + 2 * g->nsponge;
@@ -1076,6 +1206,7 @@ ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exe
   c.rsteps = (ex && ex->reverse_steps > 0) ? ex->reverse_steps : 1;
   c.fsteps = (ex && ex->forward_steps > 0) ? ex->forward_steps : 1;
   c.branches = (ex && ex->graph_branches > 0) ? ex->graph_branches : kDefaultBranches;
+  c.blk = blk_allowed(ex);
   return c;
 }
 
@@ -1186,13 +1317,40 @@ int check_exec(const fwi_exec* ex) {
   return FWI_OK;
 }
 
+uint64_t plan_key(uint64_t ikey, int what, int plain, const ExecChoice& c, int ext_h) {
+  Hasher h;
+  h.pod(ikey);
+  h.pod(what);
+  h.pod(plain);
+  h.pod(c.S);
+  h.pod(c.TZ);
+  h.pod(c.graph_steps);
+  h.pod(c.pf_fwd);
+  h.pod(c.pf_rev);
+  h.pod(c.Sr);
+  h.pod(c.TZr);
+  h.pod(c.rsteps);
+  h.pod(c.fsteps);
+  h.pod(c.branches);
+  h.pod(c.blk);
+  h.pod(ext_h);
+  return h.h;
+}
+
+int ws_check(const Plan& p, size_t ws_bytes) {
+  if (ws_bytes < p.L.total)
+    return fail(FWI_ERR_WORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, need " +
+                                       std::to_string(p.L.total));
+  return FWI_OK;
+}
+
 int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, void* ws,
              size_t ws_bytes, const float* v, const float* wavelet, int64_t wstride, hipStream_t s,
-             std::shared_ptr<Plan>& out, bool sizing_only, int ext_h = -1) {
+             std::shared_ptr<Plan>& out, bool sizing_only, int ext_h = -1, bool compact = false) {
   const int plain = ex && ex->mode == FWI_EXEC_PLAIN;
   if (int rc = check_exec(ex)) return rc;
   ExecChoice c = base_choice(g, geo, ex);
-  const int branches = c.branches;  // not tuned: the tuner times with it
+  const int branches = c.branches, blk = c.blk;  // not tuned: the tuner times with the former, without the latter
   const bool tune = !plain && ex && ex->autotune && !sizing_only;
   const uint64_t ikey = inputs_hash(g, geo);
   std::lock_guard<std::mutex> lock(g_mutex);
@@ -1223,36 +1381,56 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
     }
   }
   c.branches = branches;
-  Hasher h;
-  h.pod(ikey);
-  h.pod(what == FWI_WS_AUTOGRAD ? FWI_WS_AUTOGRAD : what);
-  h.pod(plain);
-  h.pod(c.S);
-  h.pod(c.TZ);
-  h.pod(c.graph_steps);
-  h.pod(c.pf_fwd);
-  h.pod(c.pf_rev);
-  h.pod(c.Sr);
-  h.pod(c.TZr);
-  h.pod(c.rsteps);
-  h.pod(c.fsteps);
-  h.pod(c.branches);
-  h.pod(ext_h);
-  const uint64_t key = h.h;
-  for (auto it = g_plans.begin(); it != g_plans.end(); ++it) {
-    if ((*it)->key == key) {
-      out = *it;
-      g_plans.splice(g_plans.begin(), g_plans, it);
-      return FWI_OK;
+  c.blk = compact ? 0 : blk;
+  if (c.blk && !plain && ex && ex->autotune && !(ex->shots_in_flight > 0)) {
+    // the tuned shots in flight are the z sweeps': whether the LDS-resident
+    // ones take over is decided for every shot at once, which suits them best
+    const int runs = std::min(std::max(geo->nshot, 1), 64);
+    const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
+    const bool rev = what != FWI_WS_FORWARD && what != FWI_WS_HESSIAN && what != FWI_WS_BORN;
+    if (cells > kBlkFwdCells) c.blk &= ~1;
+    if (cells > kBlkRevCells) c.blk &= ~2;
+    if (c.blk & 1) c.fsteps = 1;
+    if (c.blk & 2) c.rsteps = 1;
+    if (c.blk == 3 || (c.blk && !rev)) {
+      c.S = runs;
+      c.Sr = 0;
     }
   }
-  out = build_plan(g, geo, c, plain, what, key, ext_h);
-  out->ikey = ikey;
-  if (!sizing_only) {
-    g_plans.push_front(out);
-    while (g_plans.size() > 16) g_plans.pop_back();
+  auto find_or_build = [&](uint64_t key) {
+    for (auto it = g_plans.begin(); it != g_plans.end(); ++it) {
+      if ((*it)->key == key) {
+        out = *it;
+        g_plans.splice(g_plans.begin(), g_plans, it);
+        return;
+      }
+    }
+    out = build_plan(g, geo, c, plain, what, key, ext_h);
+    out->ikey = ikey;
+    if (!sizing_only && out->L.total <= ws_bytes) {
+      g_plans.push_front(out);
+      while (g_plans.size() > 16) g_plans.pop_back();
+    }
+  };
+  find_or_build(plan_key(ikey, what, plain, c, ext_h));
+  if (!sizing_only && c.blk && out->L.total > ws_bytes) {
+    // a workspace of the z sweeps' size: run those
+    c.blk = 0;
+    find_or_build(plan_key(ikey, what, plain, c, ext_h));
   }
   return FWI_OK;
+}
+
+// Whether a workspace holds the call: at the size fwi_workspace_bytes reports,
+// or at that of the z sweeps (get_plan then runs those).
+int size_check(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, size_t ws_bytes,
+               int ext_h = -1) {
+  std::shared_ptr<Plan> p;
+  for (bool compact : {false, true}) {
+    if (int rc = get_plan(g, geo, ex, what, nullptr, 0, nullptr, nullptr, 0, nullptr, p, true, ext_h, compact)) return rc;
+    if (ws_bytes >= p->L.total) return FWI_OK;
+  }
+  return ws_check(*p, ws_bytes);
 }
 
 int common_checks(const fwi_grid* g, const fwi_geometry* geo, const float* v, const float* wavelet,
@@ -1263,14 +1441,6 @@ int common_checks(const fwi_grid* g, const fwi_geometry* geo, const float* v, co
   if (wstride != 0 && wstride < g->nt_max) return fail(FWI_ERR_ARG, "wavelet_stride must be 0 or >= nt_max");
   return FWI_OK;
 }
-
-int ws_check(const Plan& p, size_t ws_bytes) {
-  if (ws_bytes < p.L.total)
-    return fail(FWI_ERR_WORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, need " +
-                                       std::to_string(p.L.total));
-  return FWI_OK;
-}
-
 
 // ------------------------------------------------- exact offset diagonal
 // Shots are grouped by (record length, receiver set): a group's receiver term
@@ -1375,16 +1545,18 @@ DxGeo dx_side(const fwi_geometry* geo, const DxGroup& gr, bool receivers) {
   return o;
 }
 
-ExecChoice dx_choice(const fwi_grid* g, const fwi_exec* ex, int S) {
+ExecChoice dx_choice(const fwi_grid* g, const fwi_exec* ex, int S, bool compact) {
   const int Z = g->nz + 2 * g->nsponge;
   const int TZ = (ex && ex->tile_rows > 0) ? ex->tile_rows : default_tile_rows(Z);
   const int pf = (ex && ex->prefetch > 0) ? ex->prefetch : 1;
   // direct launches: the capture pointer is not baked into any graph
-  return ExecChoice{S, TZ, 0, pf, 1, S, TZ, 1, 1};
+  ExecChoice c{S, TZ, 0, pf, 1, S, TZ, 1, 1};
+  c.blk = compact ? 0 : blk_allowed(ex) & 1;
+  return c;
 }
 
 int dx_layout(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int hmax, double fmax, int dft,
-              DxLayout& o) {
+              DxLayout& o, bool compact = false) {
   if (int rc = check_inputs(g, geo)) return rc;
   if (int rc = check_exec(ex)) return rc;
   if (g->free_surface) return fail(FWI_ERR_ARG, "the exact offset diagonal needs the absorbing top");
@@ -1408,7 +1580,7 @@ int dx_layout(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, in
       DxGeo dg = dx_side(geo, gr, side == 0);
       const int S = std::min(Sreq, std::max(dg.g.nshot, 1));
       Smax = std::max(Smax, S);
-      auto p = build_plan(g, &dg.g, dx_choice(g, ex, S), 0, FWI_WS_FORWARD, 0);
+      auto p = build_plan(g, &dg.g, dx_choice(g, ex, S, compact), 0, FWI_WS_FORWARD, 0);
       o.plan = std::max(o.plan, (size_t)p->L.total);
     }
   }
@@ -1548,11 +1720,7 @@ static int forward_impl(const fwi_grid* grid, const fwi_geometry* geom, const fw
   if (!data && geom->nshot > 0 && geom->rec_ptr[geom->nshot] > 0) return fail(FWI_ERR_ARG, "data must not be NULL");
   const int what = dv ? FWI_WS_BORN : FWI_WS_FORWARD;
   std::shared_ptr<Plan> p;
-  {
-    std::shared_ptr<Plan> sz;
-    if ((rc = get_plan(grid, geom, exec, what, nullptr, 0, nullptr, nullptr, 0, s, sz, true))) return rc;
-    if ((rc = ws_check(*sz, ws_bytes))) return rc;
-  }
+  if ((rc = size_check(grid, geom, exec, what, ws_bytes))) return rc;
   if ((rc = get_plan(grid, geom, exec, what, workspace, ws_bytes, v, wavelet, wavelet_stride, s, p, false)))
     return rc;
   if ((rc = ws_check(*p, ws_bytes))) return rc;
@@ -1584,11 +1752,7 @@ int fwi_misfit_value(const fwi_grid* grid, const fwi_geometry* geom, const fwi_e
   if (!d_obs && geom->nshot > 0 && geom->rec_ptr[geom->nshot] > 0) return fail(FWI_ERR_ARG, "d_obs must not be NULL");
   hipStream_t s = (hipStream_t)hip_stream;
   std::shared_ptr<Plan> p;
-  {
-    std::shared_ptr<Plan> sz;
-    if ((rc = get_plan(grid, geom, exec, FWI_WS_FORWARD, nullptr, 0, nullptr, nullptr, 0, s, sz, true))) return rc;
-    if ((rc = ws_check(*sz, ws_bytes))) return rc;
-  }
+  if ((rc = size_check(grid, geom, exec, FWI_WS_FORWARD, ws_bytes))) return rc;
   if ((rc = get_plan(grid, geom, exec, FWI_WS_FORWARD, workspace, ws_bytes, v, wavelet, wavelet_stride, s, p,
                      false)))
     return rc;
@@ -1644,11 +1808,7 @@ static int gradient_impl(const fwi_grid* grid, const fwi_geometry* geom, const f
   }
   if (part != 1 && !grad && !ext) return fail(FWI_ERR_ARG, "grad must not be NULL");
   std::shared_ptr<Plan> p;
-  {
-    std::shared_ptr<Plan> sz;
-    if ((rc = get_plan(grid, geom, exec, what, nullptr, 0, nullptr, nullptr, 0, s, sz, true, ext_h))) return rc;
-    if ((rc = ws_check(*sz, ws_bytes))) return rc;
-  }
+  if ((rc = size_check(grid, geom, exec, what, ws_bytes, ext_h))) return rc;
   if (part == 2) {
     // the backward half must use the plan and workspace of the forward half
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -1742,12 +1902,9 @@ int fwi_gradient_static(const fwi_grid* grid, const fwi_geometry* geom, const fw
   if (exec) ex = *exec;
   ex.graph_steps = -1;
   ex.autotune = 0;
-  const size_t need = fwi_workspace_bytes(grid, geom, &ex, FWI_WS_GRADIENT, hmax);
-  if (need == 0) return FWI_ERR_ARG;  // sizing failed (message set)
-  if (need > FWI_STATIC_SCRATCH_BYTES)
-    return fail(FWI_ERR_WORKSPACE, "fwi_gradient_static: the call needs " + std::to_string(need) +
-                                       " bytes of scratch, the static array holds " +
-                                       std::to_string((size_t)FWI_STATIC_SCRATCH_BYTES));
+  // (a call whose LDS-resident sweeps would not fit runs the z sweeps)
+  if (int rc = size_check(grid, geom, &ex, FWI_WS_GRADIENT, FWI_STATIC_SCRATCH_BYTES))
+    return rc == FWI_ERR_WORKSPACE ? fail(rc, "fwi_gradient_static: " + g_last_error) : rc;
   void* ws = nullptr;
   if (int rc = static_scratch(&ws)) return rc;
   return gradient_impl(grid, geom, &ex, v, wavelet, wavelet_stride, d_obs, misfit, J, nullptr, grad, illum, hmax,
@@ -1798,11 +1955,7 @@ int fwi_hessian_diag(const fwi_grid* grid, const fwi_geometry* geom, const fwi_e
   if ((rc = check_outputs_hess(hmax, rcv_model, D, grid))) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
   std::shared_ptr<Plan> p;
-  {
-    std::shared_ptr<Plan> sz;
-    if ((rc = get_plan(grid, geom, exec, FWI_WS_HESSIAN, nullptr, 0, nullptr, nullptr, 0, s, sz, true))) return rc;
-    if ((rc = ws_check(*sz, ws_bytes))) return rc;
-  }
+  if ((rc = size_check(grid, geom, exec, FWI_WS_HESSIAN, ws_bytes))) return rc;
   if ((rc = get_plan(grid, geom, exec, FWI_WS_HESSIAN, workspace, ws_bytes, v, wavelet, wavelet_stride, s, p,
                      false)))
     return rc;
@@ -1833,6 +1986,12 @@ int fwi_offset_diag_exact(const fwi_grid* grid, const fwi_geometry* geom, const 
   if (!diag) return fail(FWI_ERR_ARG, "diag must not be NULL");
   DxLayout o;
   if ((rc = dx_layout(grid, geom, exec, hmax, fmax, dft, o))) return rc;
+  // a workspace of exactly the size that the z sweeps need (what the sizing
+  // call reported before the LDS-resident ones) runs those
+  DxLayout z;
+  if (ws_bytes < o.total && (rc = dx_layout(grid, geom, exec, hmax, fmax, dft, z, true))) return rc;
+  const bool compact = ws_bytes < o.total && ws_bytes == z.total;
+  if (compact) o = z;
   if (ws_bytes < o.total)
     return fail(FWI_ERR_WORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, need " +
                                        std::to_string(o.total));
@@ -1879,7 +2038,7 @@ int fwi_offset_diag_exact(const fwi_grid* grid, const fwi_geometry* geom, const 
       const bool rcv = side == 0;
       DxGeo dg = dx_side(geom, gr, rcv);
       const int S = std::min(Sreq, std::max(dg.g.nshot, 1));
-      auto p = build_plan(grid, &dg.g, dx_choice(grid, exec, S), 0, FWI_WS_FORWARD, 0);
+      auto p = build_plan(grid, &dg.g, dx_choice(grid, exec, S, compact), 0, FWI_WS_FORWARD, 0);
       if (p->L.total > o.plan || p->S > o.S) return fail(FWI_ERR_STATE, "exact offset diagonal: plan outgrew its region");
       if ((rc = begin_call(*p, workspace, v, s))) return rc;
       err = &at<Header>(workspace, p->L.hdr)->err;
@@ -1899,9 +2058,17 @@ int fwi_offset_diag_exact(const fwi_grid* grid, const fwi_geometry* geom, const 
         for (int k0 = 0; k0 < Tn; k0 += o.Tc) {
           const int tc = std::min(o.Tc, Tn - k0);
           a.cap_n0 = k0;
-          for (int k = k0; k < k0 + tc; ++k) {
-            a.step = k;
-            HIP_TRY(launch_forward(a, flags, p->pf_fwd, s));
+          if (p->bf.T) {
+            BlockArgs ba = block_args(*p, workspace, a, p->bf);
+            for (int k = k0 / ba.T; k * ba.T < k0 + tc; ++k) {
+              ba.s.step = k;
+              HIP_TRY(launch_forward_block(ba, flags, s));
+            }
+          } else {
+            for (int k = k0; k < k0 + tc; ++k) {
+              a.step = k;
+              HIP_TRY(launch_forward(a, flags, p->pf_fwd, s));
+            }
           }
           DftArgs da{};
           da.X = cap;
