@@ -106,7 +106,7 @@ typedef struct {
 /* Execution settings (all fields 0 = automatic).  Where a launch of the z
  * sweeps (one wavefront walking a tile's rows) would not fill the GPU, sweeps
  * whose fields below are 0 (tile rows, prefetch, steps per launch) hold their
- * tiles in LDS and run several time steps per launch, outside graphs; the
+ * tiles in LDS and run several time steps per launch; the
  * results have the same bits as the one-step z sweeps'.  Naming one of those
  * fields selects the z sweep it belongs to. */
 typedef struct {
@@ -117,8 +117,10 @@ typedef struct {
                                  forward sweep                                 */
     int32_t tile_rows;        /* rows of one wavefront's tile (z sweep length)
                                  of the forward sweep                          */
-    int32_t graph_steps;      /* time steps per captured hipGraph chunk;
-                                 -1 = do not use graphs                        */
+    int32_t graph_steps;      /* launches of the one-step and two-step sweeps
+                                 between two folds of the extended image
+                                 (0 = 32); -1 = every sweep as one launch
+                                 chain on the caller's stream                  */
     int32_t autotune;         /* 1 = pick unset fields by timing a few steps
                                  of each candidate inside the call's workspace;
                                  the choice is cached per grid, geometry and
@@ -145,7 +147,8 @@ typedef struct {
                                  (temporal blocking: a workgroup computes the
                                  first step on 256 columns and the second on
                                  the 248 inside, one read and one write of
-                                 every field for both); 0 = tuned, else 1.
+                                 every field for both); 0 = tuned, else by
+                                 size (1 where a z-sweep field is set).
                                  Two steps are not used with a free surface,
                                  in plain mode or for the eq. (3) variant      */
     int32_t forward_steps;    /* time steps per launch of the forward sweep
@@ -153,15 +156,18 @@ typedef struct {
                                  fwi_extended_image: 1, or 2 (the same
                                  workgroup tiling; u[n+1], u[n+2], d[n+2]
                                  written once per two steps); 0 = tuned, else
-                                 1.  Not used with a free surface, in plain
-                                 mode, for Born modelling or the forward-only
-                                 calls                                         */
-    int32_t graph_branches;   /* independent launch chains that each captured
-                                 chunk of the two-step sweeps is split into,
-                                 each over a contiguous share of the launch's
-                                 shots, so that one chain's launches run in
-                                 the others' tails: 1 to 4 (at most the shots
-                                 per launch); 0 = 2                            */
+                                 by size (1 where a z-sweep field is set).  Not
+                                 used with a free surface, in plain mode or for
+                                 Born modelling; the forward-only calls choose
+                                 by themselves                                 */
+    int32_t graph_branches;   /* independent launch chains of the two-step
+                                 sweeps, each over a contiguous share of the
+                                 launch's shots on a stream of its own between
+                                 a fork from the caller's stream and a join to
+                                 it, so that one chain's launches run in the
+                                 others' tails: 1 to 4 (at most the shots per
+                                 launch); 0 = 2; 1 while the caller's stream is
+                                 being captured                                */
 } fwi_exec;
 
 enum { FWI_EXEC_BATCHED = 0, FWI_EXEC_PLAIN = 1 };

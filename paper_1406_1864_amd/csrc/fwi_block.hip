@@ -47,8 +47,6 @@ __device__ __forceinline__ float bck(int k) {
   return k == 1 ? 8.0f / 5.0f : (k == 2 ? -1.0f / 5.0f : (k == 3 ? 8.0f / 315.0f : -1.0f / 560.0f));
 }
 
-__device__ __forceinline__ int buniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
 // workgroup barrier that orders LDS only: global loads and stores in flight stay
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -339,6 +337,25 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
   if (ns <= 0) return;
   const PT p(a, d, tile);
   const int cs0 = p.xs - p.lx, rz0 = p.z - p.lz;
+  const bool src_in = sd.src_z >= rz0 && sd.src_z < rz0 + RZ && sd.src_xs >= cs0 && sd.src_xs < cs0 + RX;
+  // a region that the wavefield has not reached stays zero
+  bool track = false;
+  if (s.act) {
+    const Reached r = reached(s, si.cs, rz0, rz0 + RZ, cs0, cs0 + RX, n0);
+    if (!r.any && !src_in) {
+      if constexpr (CAP) {  // the captured series of its cells
+#pragma unroll
+        for (int i = 0; i < PZ; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (p.own_model(i, j))
+              for (int k = 0; k < ns; ++k)
+                s.cap[((int64_t)slot * s.cap_T + (n0 + k - s.cap_n0)) * s.cap_R + p.midx(d, i, j)] = 0.0f;
+      }
+      return;
+    }
+    track = !r.all;
+  }
 
   const int set_in = 3 * (q & 1), set_out = 3 - set_in;
   float* ubase = s.u + (int64_t)si.cs * s.ustride;
@@ -361,7 +378,6 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
       for (int j = 0; j < 4; ++j) ev[i][j] = (n0 > 0 && p.own_model(i, j)) ? E[p.midx(d, i, j)] : 0.0f;
   }
   const float* wave = s.wavelet + (int64_t)si.shot * s.wstride;
-  const bool src_in = sd.src_z >= rz0 && sd.src_z < rz0 + RZ && sd.src_xs >= cs0 && sd.src_xs < cs0 + RX;
   int src = -1;  // the source's cell in this patch
   if (src_in) {
     const int iz = sd.src_z - p.z, ix = sd.src_xs - p.xs;
@@ -509,6 +525,22 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
     }
   }
   const PT r = p.here();
+  if (track) {
+#pragma unroll
+    for (int i = 0; i < PZ; ++i) {
+      uint32_t any = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        any |= __float_as_uint(uc[i][j]) | __float_as_uint(dn[i][j]);
+        if constexpr (BORN) any |= __float_as_uint(bc[i][j]) | __float_as_uint(bd[i][j]);
+      }
+      // the first lane of each of the map's columns in a row of 16 lanes marks it
+      const uint64_t nz = __ballot(any != 0u && r.own_row(i));
+      const int l = threadIdx.x & 63, left = min((kActCols - (r.xs & (kActCols - 1))) / 4, 16 - (l & 15));
+      if (((l & 15) == 0 || (r.xs & (kActCols - 1)) == 0) && (nz >> l & ((1u << left) - 1)))
+        mark_reached(s, si.cs, r.z + i, r.xs, n0 + 1);
+    }
+  }
   r.store(d, ubase + (int64_t)(set_out + ((n0 + ns) & 1)) * d.field, uc);
   r.store(d, ubase + (int64_t)(set_out + 2) * d.field, dn);
   if constexpr (BORN) {
@@ -553,7 +585,6 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_reverse_block(BlockAr
   if (ns <= 0) return;
   const PT p(a, d, tile);
   const int cs0 = p.xs - p.lx, rz0 = p.z - p.lz;
-
   // u[k] at level ubi + (k & 1), lam[k] at level lbi + (k & 1)
   const int ubi = 3 * (q & 1), ubo = 3 - ubi, lbi = 2 * (q & 1), lbo = 2 - lbi;
   float* ubase = s.u + (int64_t)si.cs * s.ustride;

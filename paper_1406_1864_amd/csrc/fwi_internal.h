@@ -101,8 +101,7 @@ struct StepArgs {
   float* strip;         // [cs] blocks of strip_stride floats: [nt][ring]
   int64_t snap_stride, strip_stride;
   double sp_a;          // sponge damping g = sp_a * d^2 (d: cells into sponge)
-  const int32_t* step_ctr;  // device step base (graph replay) or null
-  int32_t step;             // step offset, or absolute step if step_ctr is null
+  int32_t step;             // launch index
   const int32_t* err;       // device error flag: nonzero = skip all work
   // extended imaging (reverse sweep only): lam[m] and D[m] of the model cells
   // are kept for the last ext_T launch steps, ring slot = step % ext_T
@@ -119,10 +118,41 @@ struct StepArgs {
   float* cap;
   int64_t cap_R;
   int32_t cap_n0, cap_T;
+  // where the source wavefield has arrived: per checkpoint set and block of
+  // kActRows x kActCols storage cells a step before which every u (du) of the
+  // block is exactly zero (INT32_MAX: zero so far); null: not kept, every
+  // tile runs every step
+  int32_t* act;
+  int32_t act_nx, act_nz;
 };
+constexpr int kActRows = 8, kActCols = 32;
 
-// Extended imaging over one window of reverse launch steps
-// [base + step0, base + step0 + count), base = *step_ctr (or 0):
+#if defined(__HIPCC__)
+// Which of the arrival map's blocks that overlap rows [z0, z1) x storage
+// columns [x0, x1) have been reached by step n (whole wavefront, uniform).
+// The kernels that fill the map in the same launch write steps above n.
+struct Reached {
+  bool any, all;
+};
+__device__ __forceinline__ Reached reached(const StepArgs& a, int cs, int z0, int z1, int x0, int x1, int n) {
+  const int32_t* p = a.act + (int64_t)cs * a.act_nx * a.act_nz;
+  const int r0 = max(z0, 0) / kActRows, r1 = min((z1 - 1) / kActRows, a.act_nz - 1);
+  const int c0 = max(x0, 0) / kActCols, c1 = min((x1 - 1) / kActCols, a.act_nx - 1);
+  const int w = c1 - c0 + 1, count = (r1 - r0 + 1) * w;
+  bool any = false, all = true;
+  for (int i = threadIdx.x & 63; i < count; i += 64) {
+    const bool in = p[(int64_t)(r0 + i / w) * a.act_nx + c0 + i % w] <= n;
+    any |= in;
+    all &= in;
+  }
+  return Reached{__ballot(any) != 0, __ballot(!all) == 0};
+}
+__device__ __forceinline__ void mark_reached(const StepArgs& a, int cs, int z, int xs, int n) {
+  atomicMin(a.act + ((int64_t)cs * a.act_nz + z / kActRows) * a.act_nx + xs / kActCols, n);
+}
+#endif
+
+// Extended imaging over one window of reverse steps [step0, step0 + count):
 //   I(x, h) += sum_slots sum_steps lam[m](x - h) D[m](x + h)
 struct ExtArgs {
   Dims d;
@@ -135,15 +165,14 @@ struct ExtArgs {
   float* I;             // [groups][2 hmax + 1][model]: one partial sum per slot group
   int32_t hmax;
   int32_t groups;       // slots are split into this many groups (parallelism)
-  const int32_t* step_ctr;  // launches done (graph replays), or null
-  int32_t step_mul;         // reverse steps per launch: the window starts at step_mul * *step_ctr + step0
   int32_t step0, count;     // in reverse steps
   const int32_t* err;
 };
 
 // reverse-kernel variants: kRevExt keeps lam and D for extended imaging;
 // kRevImgU correlates lam[m] with u[m-1] instead of D[m] (eq. (3) taken literally)
-enum : int { kRevExt = 1, kRevImgU = 2 };
+// kRevResetB (two-step sweep): some shot restarts on the launch's second step
+enum : int { kRevExt = 1, kRevImgU = 2, kRevResetB = 4 };
 
 // forward-kernel feature flags
 // kFwdBorn: also step the Born perturbation wavefield and record it instead of u
@@ -217,7 +246,9 @@ hipError_t launch_ext_image(const ExtArgs& a, hipStream_t s);
 // maps of that tiling, step = launch index); no extended image, eq. (3) or
 // free surface
 hipError_t launch_reverse2(const StepArgs& a, int prefetch, int flags, hipStream_t s);
-hipError_t launch_forward2(const StepArgs& a, int prefetch, hipStream_t s);
+hipError_t launch_forward2(const StepArgs& a, int flags, int prefetch, hipStream_t s);
+// the arrival maps of the slots' checkpoint sets to "not reached"
+hipError_t launch_act_reset(int32_t* act, int64_t count, const SlotInfo* slots, int S, hipStream_t s);
 // after a forward sweep of spl steps per launch: shots whose final state sits
 // in the second set of u levels (an odd number of launches) get it copied to
 // the first
@@ -225,7 +256,6 @@ hipError_t launch_forward2_finish(float* u, int64_t ustride, int64_t set_floats,
                                   const ShotDesc* shots, int S, int spl, hipStream_t s);
 hipError_t launch_ext_out(const Dims& d, const float* Iacc, int groups, int hmax, const float* v, float* image,
                           const int32_t* err, hipStream_t s);
-hipError_t launch_advance(int32_t* ctr, int32_t by, hipStream_t s);
 hipError_t launch_set(int32_t* ctr, int32_t value, hipStream_t s);
 hipError_t launch_misfit(const MisfitArgs& a, int S, int max_nrec, hipStream_t s);
 hipError_t launch_reduce_J(const double* part, int n, double* J, const int32_t* err, hipStream_t s);

@@ -86,9 +86,6 @@ __device__ __forceinline__ bool map_tile(const Dims& d, int S, int xcd_map, int 
   return slot < S && tile < T;
 }
 
-__device__ __forceinline__ int step_of(const StepArgs& a) {
-  return a.step_ctr ? (*a.step_ctr + a.step) : a.step;
-}
 
 // Per-lane column classification of a wavefront tile (computed once).
 struct Col {
@@ -217,7 +214,7 @@ __global__ __launch_bounds__(256) void k_forward(StepArgs a) {
   const SlotInfo si = a.slots[slot];
   if (si.shot < 0) return;
   const ShotDesc sd = a.shots[si.shot];
-  const int n = step_of(a);
+  const int n = a.step;
   if (n >= sd.nt - 1) return;
 
   const Dims& d = a.d;
@@ -438,7 +435,7 @@ __global__ __launch_bounds__(256) void k_reverse(StepArgs a) {
   const SlotInfo si = a.slots[slot];
   if (si.shot < 0) return;
   const ShotDesc sd = a.shots[si.shot];
-  const int m = sd.nt - 1 - step_of(a);
+  const int m = sd.nt - 1 - a.step;
   if (m < 1) return;
 
   const Dims& d = a.d;
@@ -472,7 +469,7 @@ __global__ __launch_bounds__(256) void k_reverse(StepArgs a) {
   const float* strip = (m >= 3) ? a.strip + (int64_t)si.cs * a.strip_stride + (int64_t)(m - 2) * d.ring
                                 : nullptr;
   const bool first = (m == sd.nt - 1);
-  const int ext_slot = EXT ? step_of(a) % a.ext_T : 0;
+  const int ext_slot = EXT ? a.step % a.ext_T : 0;
   float* G = a.g + (int64_t)slot * d.model;
   float* E = a.E + (int64_t)slot * d.model;
 
@@ -620,10 +617,10 @@ __global__ __launch_bounds__(256) void k_reverse(StepArgs a) {
 // stencil, beside A's input window, which also holds B's point-wise operands
 // u[m-1], lam[m+1].  The sweep reads one pair of u and lam levels and writes
 // the other pair (alternating from launch to launch), because neighbouring
-// workgroups read the inputs in their overlap.  Snapshot restarts fall on A
-// (even snapshot spacing); the launch before a restart stores the snapshot's
-// u[a_k], u[a_k - 1] into the model cells of the levels it writes, so no
-// launch reads snapshots.  Launch q runs A at m = nt-1-2q; B is skipped when
+// workgroups read the inputs in their overlap.  A snapshot restart on A: the
+// launch before it stores the snapshot's u[a_k], u[a_k - 1] into the model
+// cells of the levels it writes; on B: A's results and B's operand are
+// replaced by the pair.  Launch q runs A at m = nt-1-2q; B is skipped when
 // m = 1.
 // A row whose update is the plain interior FMA on every lane of a wavefront
 // (a model row of columns inside the model, without receiver or source)
@@ -670,7 +667,9 @@ __device__ __forceinline__ bool idle_wave(const Dims& d, int xs0, int wv) {
 
 // (at least 4 wavefronts per SIMD: the compiler keeps the deeper prefetch
 // within 128 VGPRs)
-template <int PF, bool EXT>
+// RESETB: the launch may restart a shot on B (a variant of its own: its code
+// in every launch made the sweep 10 % slower)
+template <int PF, bool EXT, bool RESETB>
 __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
   // PF: rows of loads in flight ahead of A (1 or 3)
   constexpr int W = PF == 1 ? 10 : 12;  // register rings: the unrolled period
@@ -690,7 +689,7 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
   const SlotInfo si = a.slots[slot];
   if (si.shot < 0) return;
   const ShotDesc sd = a.shots[si.shot];
-  const int q = step_of(a);
+  const int q = a.step;
   const int m = sd.nt - 1 - 2 * q;  // step A
   if (m < 1) return;
   const bool hasB = m >= 2;
@@ -761,6 +760,14 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
   const int32_t osA = hasSA ? (int32_t)((int64_t)(m - 2) * d.ring * 4) : 0;
   const int32_t osB = hasSB ? (int32_t)((int64_t)(m - 3) * d.ring * 4) : 0;
   const bool first = (m == sd.nt - 1);
+  // a snapshot restart on B (an odd multiple of an odd spacing): B's inputs
+  // u[m-1] and u[m-2] of the model cells are the pair's
+  const int remB = sd.nt - m;
+  const bool resetB = RESETB && hasB && remB % sd.K == 0 && remB / sd.K <= sd.nsnap;
+  auto snapB = [&](int which, int mz) {
+    return a.snap[(int64_t)si.cs * a.snap_stride + ((int64_t)(remB / sd.K - 1) * 2 + which) * d.model +
+                  (int64_t)mz * d.nx + col.mx];
+  };
 
   const bool src_tile = sd.src_z >= za0 && sd.src_z < za1 && sd.src_xs >= xs0 && sd.src_xs < xs0 + kWave;
   const int src_row = src_tile ? sd.src_z : INT_MIN;
@@ -886,7 +893,7 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
       {
         const float w = wr[sA], cu = uc[sA], cl = lc[sA];
         float lo_ = 0.0f, uo_ = 0.0f, d_ = 0.0f;
-        if (tile_int && z >= mz_lo && z < mz_hi && z != rzA && z != src_row) {
+        if (tile_int && z >= mz_lo && z < mz_hi && z != rzA && z != src_row && !resetB) {
           lo_ = fmaf(w, lapL, 2.0f * cl - pl[qa]);
           d_ = w * lapU;
           uo_ = fmaf(w, lapU, 2.0f * cu - p0[qa]);
@@ -903,7 +910,7 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
           if (col.xin && dd == 0) {
             lo_ = fmaf(w, lapL, 2.0f * cl - pl[qa]);
             d_ = w * lapU;
-            uo_ = fmaf(w, lapU, 2.0f * cu - p0[qa]);
+            uo_ = resetB ? snapB(1, row.mz) : fmaf(w, lapU, 2.0f * cu - p0[qa]);
           } else if (col.xin) {
             lo_ = sponge_update(a.sp_a, dd, cl, pl[qa], w, lapL);
             if (hasSA && strip_index(row, col) >= 0) uo_ = sa[qa];
@@ -931,7 +938,7 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
         const float w = wr[sB], cu = uo[sB], cl = lo[sB], pu = uc[sB], pl1 = lc[sB], da = dA[sB];
         float l1 = 0.0f, u1 = 0.0f, gn = 0.0f, en = 0.0f, dB = 0.0f;
         bool st_l = own_col, st_u = own_col, st_g = own_col;
-        if (tile_int && zbB >= mz_lo && zbB < mz_hi && zbB != rzB && zbB != src_row && hasB) {
+        if (tile_int && zbB >= mz_lo && zbB < mz_hi && zbB != rzB && zbB != src_row && hasB && !resetB) {
           l1 = fmaf(w, lapLB, 2.0f * cl - pl1);
           const float D = w * lapUB;
           dB = D;
@@ -956,7 +963,7 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
             l1 = fmaf(w, lapLB, 2.0f * cl - pl1);
             const float D = w * lapUB;
             dB = D;
-            u1 = fmaf(w, lapUB, 2.0f * cu - pu);
+            u1 = fmaf(w, lapUB, 2.0f * cu - (resetB ? snapB(0, row.mz) : pu));
             gn = hasB ? fmaf(l1, D, ag) : ag;
             en = hasB ? fmaf(D, D, ae) : ae;
             st_u = st_l;
@@ -1003,8 +1010,8 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
 }
 
 // -------------------------------------------------------------------------
-// Two forward steps per launch for the gradient's forward sweep (recording,
-// checkpoints; no free surface), A = step n -> n+1 and B = step n+1 -> n+2,
+// Two forward steps per launch (recording, with or without checkpoints;
+// illumination; captured series; no free surface), A = step n -> n+1 and B = step n+1 -> n+2,
 // with the workgroup tiling of the two-step reverse sweep: A on 256 columns,
 // B on the 248 inside them, rows exchanged through LDS with one barrier per
 // row, A 4 rows ahead of B and over 4 more rows on either side of the band,
@@ -1016,8 +1023,10 @@ __global__ __launch_bounds__(256, 4) void k_reverse2(StepArgs a) {
 // number of steps) stores u[n], u[n+1], d[n+1] instead.  Strips, snapshots and traces are written by the step
 // that produces them, as in the one-step sweep.
 // -------------------------------------------------------------------------
-template <int PF>
+template <int PF, int FLAGS>
 __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
+  constexpr bool REC = (FLAGS & kFwdRecord) != 0, CKPT = (FLAGS & kFwdCkpt) != 0, ILLUM = (FLAGS & kFwdIllum) != 0;
+  constexpr bool CAP = (FLAGS & (kFwdCapD | kFwdCapU)) != 0;
   constexpr int W = PF == 1 ? 10 : 12;  // register rings: the unrolled period
   constexpr int R = PF + 1;             // point-wise rings
   static_assert(W >= 9 + PF && W % R == 0, "ring lengths must fit the window and the unrolled period");
@@ -1034,13 +1043,13 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
   const SlotInfo si = a.slots[slot];
   if (si.shot < 0) return;
   const ShotDesc sd = a.shots[si.shot];
-  const int q = step_of(a);
+  const int q = a.step;
   const int n = 2 * q;  // step A: n -> n+1
   if (n >= sd.nt - 1) return;
   const bool hasB = n + 1 < sd.nt - 1;
   // u[n+1] is stored only by the shot's last launch (the reverse sweep starts
   // from u[nt-1], u[nt-2]); the next launch reads u[n+2] and d[n+2] only
-  const bool keep1 = n + 2 >= sd.nt - 1;
+  const bool keep1 = CKPT && n + 2 >= sd.nt - 1;
 
   const Dims& d = a.d;
   const int xt = tile % d.XT, zt = tile / d.XT;  // xt % 4 == wv
@@ -1059,6 +1068,29 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
   const int za0 = z0 - kRadius, za1 = z1 + kRadius;    // A's rows
   const int mz_lo = d.N, mz_hi = d.N + d.nz;
   const bool tile_int = xs0 >= d.mx0 && xs0 + kWave <= d.mx0 + d.nx;
+  // a tile that the wavefield has not come within 8 cells of stays zero for
+  // these two steps: what it would write is zero already (its levels) or was
+  // cleared before the sweep (strips, snapshots, traces, E)
+  bool track = false;
+  if (a.act) {
+    const int xo = xs0 - kWave * wv + kRadius;
+    const Reached r = reached(a, si.cs, z0 - 2 * kRadius, z1 + 2 * kRadius, xo - 2 * kRadius, xo + kBlk2 + 2 * kRadius, n);
+    const bool src = sd.src_z >= z0 - 2 * kRadius && sd.src_z < z1 + 2 * kRadius && sd.src_xs >= xo - 2 * kRadius &&
+                     sd.src_xs < xo + kBlk2 + 2 * kRadius;
+    if (!r.any && !src) {
+      if (CAP) {  // the captured series of the tile's cells
+        float* c0 = a.cap + ((int64_t)slot * a.cap_T + (n - a.cap_n0)) * a.cap_R;
+        if (own_col && col.mcol)
+          for (int z = max(z0, mz_lo); z < min(z1, mz_hi); ++z) {
+            const int64_t mi = (int64_t)(z - d.N) * d.nx + col.mx;
+            c0[mi] = 0.0f;
+            if (hasB) c0[a.cap_R + mi] = 0.0f;
+          }
+      }
+      return;
+    }
+    track = !r.all && hasB;
+  }
 
   // level sets: launch q reads set q & 1 and writes the other
   const int si_ = 3 * (q & 1), so_ = 3 - si_;
@@ -1091,8 +1123,8 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
   const int dz = (zt & 1) ? -1 : 1;
   const int zA0 = dz > 0 ? za0 : za1 - 1;
   const int nA = za1 - za0;
-  int rpA, rpB, rbeg, rend;
-  {
+  int rpA = 0, rpB = 0, rbeg = 0, rend = 0;
+  if (REC) {
     const RmapDir dir = a.rdir[sd.rdir2 + xt];
     rbeg = dir.begin;
     rend = dir.begin + dir.count;
@@ -1121,6 +1153,13 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
   float uo[W], dq[W];   // A's results u[n+1], d[n+1]: positions j-9 .. j
   float wr[W];          // w: positions j-4 .. j+PF (B uses A's loads 4 rows later)
   float uh[R], pd[R];   // A's halo column, d[n]
+  float dA[ILLUM ? W : 1];  // A's D = w L u[n]: positions j-9 .. j
+  float eB[ILLUM ? R : 1];  // E of B's row
+  float* E = ILLUM ? a.E + (int64_t)slot * d.model : nullptr;
+  const rsrc_t rE = make_rsrc(ILLUM ? E : a.w, ILLUM ? d.model : 1);
+  const uint32_t om = (uint32_t)col.mxc * 4u;
+  auto mrow4 = [&](int r) { return (int32_t)(min(max(r - d.N, 0), d.nz - 1) * d.nx * 4); };
+  uint32_t acc = 0;  // bits of the lane's results in the arrival map's current rows
   auto load_ptA = [&](int r, float& hu, float& dn, float& w) {
     hu = bld(rU, oh, ouIn + r * P4);
     const int rc = clamp_row(d, r);
@@ -1135,6 +1174,12 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
   for (int j = 0; j < PF; ++j) load_ptA(zA0 + dz * j, uh[j], pd[j], wr[(j + 4) % W]);
 #pragma unroll
   for (int j = 0; j < W; ++j) uo[j] = dq[j] = 0.0f;
+  if constexpr (ILLUM) {
+#pragma unroll
+    for (int j = 0; j < W; ++j) dA[j] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < PF; ++j) eB[j] = bld(rE, om, mrow4(zA0 + dz * kRadius));
+  }
 
   for (int jb = 0; jb < nA; jb += W) {
     static_for<W>([&](auto rc) __attribute__((always_inline)) {
@@ -1146,6 +1191,7 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
       {
         const int qn = (r + PF) % R;
         load_ptA(z + dz * PF, uh[qn], pd[qn], wr[(r + 4 + PF) % W]);
+        if constexpr (ILLUM) eB[qn] = bld(rE, om, mrow4(zA0 + dz * (max(j + PF, 2 * kRadius) - kRadius)));
       }
       const int sA = (r + 4) % W, sB = r % W, qa = r % R;
       float(*xr)[LR] = xrow[r & 1];
@@ -1161,7 +1207,7 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
         const float c = uc[sA], dn = pd[qa], w = wr[sA];
         float out = 0.0f, dnew = 0.0f;
         const bool own_row = z >= z0 && z < z1;
-        if (tile_int && z >= mz_lo && z < mz_hi && z != rzA && z != src_row && !saveA) {
+        if (tile_int && z >= mz_lo && z < mz_hi && z != rzA && z != src_row && !(CKPT && saveA)) {
           dnew = fmaf(w, lap, dn);
           out = c + dnew;
         } else if (z >= 0 && z < d.Z) {
@@ -1176,7 +1222,7 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
               dnew = (float)(((1.0 - gm) * (double)dn + (double)w * (double)lap) / (1.0 + gm));
             }
             out = c + dnew;
-            if (own_row && own_col) {
+            if (CKPT && own_row && own_col) {
               const int ri = strip_index(row, col);
               if (ri >= 0) stripA[ri] = out;
               if (saveA && row.model && col.mcol) {
@@ -1186,30 +1232,39 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
               }
             }
           }
-          if (z == rzA) {
+          if (REC && z == rzA) {
             const int tr = a.rmaps[a.rrows[rpA].map + lane];
             if (tr >= 0 && own_col) trA[tr] = out;
             rpA += dz;
             rzA = rz_at(rpA);
           }
         }
+        if (CAP && own_row && own_col && z >= mz_lo && z < mz_hi && col.mcol)
+          a.cap[((int64_t)slot * a.cap_T + (n - a.cap_n0)) * a.cap_R + (int64_t)(z - d.N) * d.nx + col.mx] =
+              (FLAGS & kFwdCapD) ? w * lap : out;
         if (own_row && own_col) {
           if (keep1) bst(rU, oc, ouO1 + z * P4, out);
-          if (!hasB) {
+          if (CKPT && !hasB) {
             bst(rU, oc, ouO0 + z * P4, c);
             bst(rU, oc, odO + z * P4, dnew);
           }
         }
         uo[sA] = out;
         dq[sA] = dnew;
+        if constexpr (ILLUM) dA[sA] = w * lap;
       }
       // ---- step B at row z - 4 dz, from sweep position 8 on
       const int zbB = z - dz * kRadius;
+      if constexpr (ILLUM) {
+        // (a shot's last launch may end after A)
+        if (!hasB && j >= 2 * kRadius && own_col && zbB >= mz_lo && zbB < mz_hi && col.mcol)
+          bst(rE, om, mrow4(zbB), fmaf(dA[sB], dA[sB], eB[r % R]));
+      }
       if (hasB && j >= 2 * kRadius) {
         float lap = laplace<W>(uo, r, xr[1] + kWave * wv, lane);
         const float c = uo[sB], dn = dq[sB], w = wr[sB];
         float out, dnew;
-        if (tile_int && zbB >= mz_lo && zbB < mz_hi && zbB != rzB && zbB != src_row && !saveB) {
+        if (tile_int && zbB >= mz_lo && zbB < mz_hi && zbB != rzB && zbB != src_row && !(CKPT && saveB)) {
           dnew = fmaf(w, lap, dn);
           out = c + dnew;
         } else {
@@ -1223,7 +1278,7 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
             dnew = (float)(((1.0 - gm) * (double)dn + (double)w * (double)lap) / (1.0 + gm));
           }
           out = c + dnew;
-          if (own_col) {
+          if (CKPT && own_col) {
             const int ri = strip_index(row, col);
             if (ri >= 0) stripB[ri] = out;
             if (saveB && row.model && col.mcol) {
@@ -1232,7 +1287,7 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
               snB0[d.model + mi] = c;
             }
           }
-          if (zbB == rzB) {
+          if (REC && zbB == rzB) {
             const int tr = a.rmaps[a.rrows[rpB].map + lane];
             if (tr >= 0 && own_col) trB[tr] = out;
             rpB += dz;
@@ -1242,6 +1297,26 @@ __global__ __launch_bounds__(256, 4) void k_forward2(StepArgs a) {
         if (own_col) {
           bst(rU, oc, ouO0 + zbB * P4, out);
           bst(rU, oc, odO + zbB * P4, dnew);
+        }
+        if ((ILLUM || CAP) && own_col && zbB >= mz_lo && zbB < mz_hi && col.mcol) {
+          const float D = w * lap;
+          if constexpr (ILLUM) bst(rE, om, mrow4(zbB), fmaf(D, D, fmaf(dA[sB], dA[sB], eB[r % R])));
+          if (CAP)
+            a.cap[((int64_t)slot * a.cap_T + (n + 1 - a.cap_n0)) * a.cap_R + (int64_t)(zbB - d.N) * d.nx + col.mx] =
+                (FLAGS & kFwdCapD) ? D : out;
+        }
+        if (track) {
+          acc |= own_col ? __float_as_uint(out) | __float_as_uint(dnew) : 0u;
+          // at the end of the arrival map's rows, its columns' first lanes
+          // mark the blocks with a nonzero value
+          const int zn = zbB + dz;
+          if (zn / kActRows != zbB / kActRows || zn < z0 || zn >= z1) {
+            const uint64_t nz = __ballot(acc != 0u);
+            const int left = kActCols - (col.xs & (kActCols - 1));  // lanes up to the block's end
+            if (nz && (lane == 0 || left == kActCols) && (nz >> lane & (left >= 32 ? 0xffffffffull : (1ull << left) - 1)))
+              mark_reached(a, si.cs, zbB, col.xs, n + 1);
+            acc = 0u;
+          }
         }
       }
     });
@@ -1273,7 +1348,7 @@ __global__ __launch_bounds__(256) void k_ext_image(ExtArgs a) {
   float* shL = shL_all[wv];
   float* shD = shD_all[wv];
   const int H = a.hmax;
-  const int j0 = (a.step_ctr ? a.step_mul * *a.step_ctr : 0) + a.step0;
+  const int j0 = a.step0;
   float acc[2 * HM + 1];
 #pragma unroll
   for (int h = 0; h < 2 * HM + 1; ++h) acc[h] = 0.0f;
@@ -1333,7 +1408,7 @@ __global__ __launch_bounds__(256) void k_ext_image4(ExtArgs a) {
   const int spg = (a.S + a.groups - 1) / a.groups;
   const int s_lo = grp * spg, s_hi = min(a.S, s_lo + spg);
   const int H = a.hmax;
-  const int j0 = (a.step_ctr ? a.step_mul * *a.step_ctr : 0) + a.step0;
+  const int j0 = a.step0;
   const int n_it = max(s_hi - s_lo, 0) * a.count;
   float* shL = shL_all[wv];
   float* shD = shD_all[wv];
@@ -1459,7 +1534,6 @@ __global__ void k_fill_slots(float* base, int64_t stride, int64_t count, const S
     p[k] = 0.0f;
 }
 
-__global__ void k_advance(int32_t* ctr, int32_t by) { *ctr += by; }
 __global__ void k_set(int32_t* ctr, int32_t value) { *ctr = value; }
 
 // misfit of one trace per thread; psi' = psi * h^2/dt^2 written in place.
@@ -1729,10 +1803,37 @@ hipError_t launch_reverse(const StepArgs& a, int prefetch, int flags, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_forward2(const StepArgs& a, int prefetch, hipStream_t s) {
+template <int FLAGS>
+static void forward2_pf(const StepArgs& a, int prefetch, hipStream_t s) {
   const dim3 grid(step_blocks(a.d, a.S)), block(256);
-  if (prefetch == 3) hipLaunchKernelGGL(k_forward2<3>, grid, block, 0, s, a);
-  else hipLaunchKernelGGL(k_forward2<1>, grid, block, 0, s, a);
+  if (prefetch == 3) hipLaunchKernelGGL((k_forward2<3, FLAGS>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_forward2<1, FLAGS>), grid, block, 0, s, a);
+}
+
+hipError_t launch_forward2(const StepArgs& a, int flags, int prefetch, hipStream_t s) {
+  if ((flags & (kFwdCapD | kFwdCapU)) && !a.cap) return hipErrorInvalidValue;
+  switch (flags) {
+    case kFwdRecord | kFwdCkpt: forward2_pf<kFwdRecord | kFwdCkpt>(a, prefetch, s); break;
+    case kFwdRecord: forward2_pf<kFwdRecord>(a, prefetch, s); break;
+    case kFwdIllum: forward2_pf<kFwdIllum>(a, prefetch, s); break;
+    case kFwdCapD: forward2_pf<kFwdCapD>(a, prefetch, s); break;
+    case kFwdCapU: forward2_pf<kFwdCapU>(a, prefetch, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+__global__ void k_act_reset(int32_t* act, int64_t count, const SlotInfo* slots) {
+  const SlotInfo si = slots[blockIdx.y];
+  if (si.shot < 0) return;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < count; k += (int64_t)gridDim.x * blockDim.x)
+    act[(int64_t)si.cs * count + k] = INT_MAX;
+}
+
+hipError_t launch_act_reset(int32_t* act, int64_t count, const SlotInfo* slots, int S, hipStream_t s) {
+  if (S <= 0 || count <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_act_reset, dim3((unsigned)std::min<int64_t>((count + 255) / 256, 64), S), dim3(256), 0, s, act,
+                     count, slots);
   return hipGetLastError();
 }
 
@@ -1760,13 +1861,15 @@ hipError_t launch_forward2_finish(float* u, int64_t ustride, int64_t set_floats,
 
 hipError_t launch_reverse2(const StepArgs& a, int prefetch, int flags, hipStream_t s) {
   const dim3 grid(step_blocks(a.d, a.S)), block(256);
-  const bool ext = (flags & kRevExt) != 0;
-  if (prefetch == 3) {
-    if (ext) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reverse2<3, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reverse2<3, false>), grid, block, 0, s, a);
-  } else {
-    if (ext) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reverse2<1, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_reverse2<1, false>), grid, block, 0, s, a);
+  switch ((prefetch == 3 ? 4 : 0) + ((flags & kRevExt) ? 2 : 0) + ((flags & kRevResetB) ? 1 : 0)) {
+    case 0: hipLaunchKernelGGL((k_reverse2<1, false, false>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_reverse2<1, false, true>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_reverse2<1, true, false>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_reverse2<1, true, true>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((k_reverse2<3, false, false>), grid, block, 0, s, a); break;
+    case 5: hipLaunchKernelGGL((k_reverse2<3, false, true>), grid, block, 0, s, a); break;
+    case 6: hipLaunchKernelGGL((k_reverse2<3, true, false>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_reverse2<3, true, true>), grid, block, 0, s, a); break;
   }
   return hipGetLastError();
 }
@@ -1795,11 +1898,6 @@ hipError_t launch_ext_out(const Dims& d, const float* Iacc, int groups, int hmax
   const int nh = 2 * hmax + 1;
   hipLaunchKernelGGL(k_ext_out, dim3(blocks_for(d.model * nh, 256)), dim3(256), 0, s, d, Iacc, groups, nh, v,
                      image, err);
-  return hipGetLastError();
-}
-
-hipError_t launch_advance(int32_t* ctr, int32_t by, hipStream_t s) {
-  hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, s, ctr, by);
   return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
 // Host runtime of libfwi: validation, execution plans, workspace layout,
-// batched time loops (direct launches or replayed hipGraph chunks), the
-// autotuner and the C ABI of include/fwi.h.
+// batched time loops, the autotuner and the C ABI of include/fwi.h.
 //
 // A plan fixes everything that depends only on the grid, the acquisition
 // geometry and the execution settings: padded storage layout, the shot ->
@@ -8,8 +7,7 @@
 // per-shot descriptors (record length, snapshot spacing K = ceil(sqrt(nt)),
 // source cell, receiver range, aperture), the receiver tile maps and the
 // byte layout of the caller's workspace.  Plans are cached by a hash of
-// those inputs; captured graphs are cached inside their plan, keyed by the
-// device pointers they bake in.
+// those inputs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -124,7 +122,7 @@ enum Phase { kPhaseFwd = 0, kPhaseRev = 1 };
 
 struct Layout {
   size_t hdr, shots, slots, rdir, rrows, rmaps, trace_shot;
-  size_t w, traces, jpart, u, lam, g, E, snap, strip, xlam, xD, xI, bu, bw, rslots, rdir2, rrows2, rmaps2, rcell, total;
+  size_t w, traces, jpart, u, lam, g, E, snap, strip, xlam, xD, xI, bu, bw, rslots, rdir2, rrows2, rmaps2, rcell, act, total;
 };
 
 // tiling of the LDS-resident sweeps (fwi_block.hip); T = 0: z sweeps
@@ -135,9 +133,8 @@ struct BlkPlan {
 // device header at the start of every workspace
 struct Header {
   int32_t err;       // device error flag
-  int32_t step;      // step counter of replayed graph chunks
   uint32_t maxbits;  // preconditioner max reduction
-  int32_t pad[61];
+  int32_t pad[62];
 };
 
 struct Plan {
@@ -155,7 +152,9 @@ struct Plan {
   int born = 0;                // Born perturbation wavefield buffers present
   int rev_steps = 1;           // time steps per launch of the plain reverse sweep (1 or 2)
   int fwd_steps = 1;           // time steps per launch of the gradient's forward sweep (1 or 2)
-  int branches = 1;            // independent chains per captured chunk of a two-step sweep
+  int branches = 1;            // independent launch chains of a two-step sweep
+  bool act_f = false;          // the forward sweep keeps its arrival map and skips tiles
+  int act_nx = 0, act_nz = 0;
   BlkPlan bf, br;              // LDS-resident forward / reverse sweeps (T = 0: off)
   int ulevels = kULevels, llevels = kLamLevels, blevels = kULevels;
   int XT2 = 0;                 // tiles of the two-step reverse sweep along x
@@ -179,14 +178,10 @@ struct Plan {
   std::vector<int2> rcell;     // (padded row, storage column) of every receiver
   int64_t snap_stride = 0, strip_stride = 0;
   Layout L{};
-  std::map<std::vector<uint64_t>, hipGraphExec_t> graphs;
   // split-mode state: workspace, v and wavelet of the last fwi_misfit_forward
   const void* fwd_ws = nullptr;
   const void* fwd_v = nullptr;
   const void* fwd_wavelet = nullptr;
-  ~Plan() {
-    for (auto& kv : graphs) hipGraphExecDestroy(kv.second);
-  }
 };
 
 // Launch configuration: the forward sweep's shots in flight / rows per tile
@@ -194,21 +189,17 @@ struct Plan {
 // reverse sweep's time steps per launch (1 or 2).
 struct ExecChoice {
   int S, TZ, graph_steps, pf_fwd, pf_rev, Sr, TZr, rsteps, fsteps;
-  int branches = 0;  // independent chains per captured two-step chunk (0: kDefaultBranches)
+  int branches = 0;  // independent launch chains of the two-step sweeps (0: kDefaultBranches)
+  int even_k = 0;    // snapshot spacing rounded up to even
   int blk = 0;       // LDS-resident sweeps where blk_tiling() has one: 1 forward, 2 reverse
 };
 
 std::mutex g_mutex;
 std::list<std::shared_ptr<Plan>> g_plans;  // most recent first
 std::map<std::vector<uint64_t>, ExecChoice> g_tuned;
-hipStream_t g_capture_stream = nullptr;
-std::mutex g_capture_mutex;  // graph capture (run_steps)
-// further capture streams and the fork/join events of chunks captured as
-// independent branches
+// launch chains of the two-step sweeps
 constexpr int kMaxBranches = 4;
 constexpr int kDefaultBranches = 2;
-hipStream_t g_branch_stream[kMaxBranches] = {};
-hipEvent_t g_fork = nullptr, g_join[kMaxBranches] = {};
 
 int shot_nt(const fwi_grid* g, const fwi_geometry* geo, int s) { return geo->nt ? geo->nt[s] : g->nt_max; }
 
@@ -307,7 +298,7 @@ bool blk_fit(const Dims& d, int shape, int T, BlkPlan& b) {
 //   reverse    3.7 / 12.2 4.3 / 13.1 7.5 / 13.7 20.1 / 18.8 32.5 / 28.9 67.6 / 47.0
 // The z sweeps' floor is their rows' latency; past the lines below they move
 // fewer bytes and repeat less work at the tiles' margins.
-constexpr int64_t kBlkFwdCells = 8000000, kBlkRevCells = 2200000;
+constexpr int64_t kBlkFwdCells = 8000000, kBlkRevCells = 1600000;
 constexpr int kBlkCUs = 256;
 
 // chunked: launches end at every 32nd step (windows of captured series or of
@@ -367,8 +358,8 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   p->rev_steps = rev2 ? 2 : 1;
   // two forward steps per launch: the gradient's forward sweep (recording and
   // checkpoints), not with a free surface; two sets of (u, u, d) levels
-  const bool fwd2 = (what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE) && !plain &&
-                    !g->free_surface && ex.fsteps == 2;
+  const bool fwd2 = (what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE ||
+                     what == FWI_WS_FORWARD || what == FWI_WS_HESSIAN) && !plain && !g->free_surface && ex.fsteps == 2;
   p->fwd_steps = fwd2 ? 2 : 1;
   p->branches = ex.branches > 0 ? ex.branches : kDefaultBranches;
   p->ulevels = fwd2 ? 2 * kULevels : (rev2 ? kULevels2 : kULevels);
@@ -386,6 +377,12 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
     if (p->br.T) p->llevels = kLamLevels2;
     if (p->bf.T) p->blevels = 2 * kULevels;
   }
+  // The arrival map pays where a launch has more tiles than run at once: a
+  // tile skipped then is time saved; below that it is one more dependent
+  // load (0.5 us of a launch's 10).
+  p->act_nx = (d.P + kActCols - 1) / kActCols;
+  p->act_nz = (d.Z + kActRows - 1) / kActRows;
+  p->act_f = fwd2 || (p->bf.T && (int64_t)p->bf.nbx * p->bf.nbz * p->S > kBlkCUs);
   p->XT2 = kWavesPerBlock * ((d.X + kBlk2 - 1) / kBlk2);
   const double eta_max = 3.0 * g->v_ref * std::log(1e3) / (2.0 * d.N * g->dx);
   p->sp_a = 0.5 * g->dt * eta_max / ((double)d.N * d.N);
@@ -402,7 +399,7 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
     std::memset(&sd, 0, sizeof(sd));
     sd.nt = shot_nt(g, geo, s);
     sd.K = std::max(1, (int)std::ceil(std::sqrt((double)sd.nt)));
-    if (rev2) sd.K += sd.K & 1;  // two-step reverse: restarts fall on the first step of a launch
+    if (ex.even_k) sd.K += sd.K & 1;
     sd.nsnap = (sd.nt - 2) / sd.K;
     max_nsnap = std::max(max_nsnap, sd.nsnap);
     sd.src_z = geo->src_iz[s] + d.N;
@@ -524,9 +521,10 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   p->born = (what == FWI_WS_BORN || what == FWI_WS_GNHVP) ? 1 : 0;
   const bool ext = (what == FWI_WS_EXTIMAGE && ext_h >= 0);
   p->ext_h = ext ? ext_h : -1;
-  // the ring holds the reverse steps of one graph chunk (two per launch for
-  // the two-step sweep)
-  p->ext_T = ext ? (p->graph_steps > 0 && !p->br.T ? p->graph_steps : 32) * p->rev_steps : 0;
+  // the ring holds the reverse steps of graph_steps launches (untuned calls:
+  // graph_steps steps, whatever form runs the sweep)
+  const int win = p->graph_steps > 0 && !p->br.T ? p->graph_steps : 32;
+  p->ext_T = !ext ? 0 : ex.even_k ? win * p->rev_steps : (win + p->rev_steps - 1) / p->rev_steps * p->rev_steps;
   Layout& L = p->L;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -546,6 +544,7 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   L.rmaps2 = take(sizeof(int32_t) * p->rmaps2.size());
   L.trace_shot = take(sizeof(int32_t) * p->trace_shot.size());
   L.rcell = take(sizeof(int2) * p->rcell.size());
+  L.act = take(p->act_f ? sizeof(int32_t) * (size_t)p->act_nx * p->act_nz * p->ncs : 0);
   L.w = take(sizeof(float) * d.field);
   L.traces = take(sizeof(float) * (size_t)g->nt_max * std::max(p->ntrace, 1));
   L.jpart = take(sizeof(double) * std::max(p->ntrace, 1));
@@ -605,12 +604,14 @@ StepArgs step_args(const Plan& p, void* ws, int batch, int phase, const float* w
   a.snap_stride = p.snap_stride;
   a.strip_stride = p.strip_stride;
   a.sp_a = p.sp_a;
-  a.step_ctr = nullptr;
   a.step = 0;
   a.err = &at<Header>(ws, p.L.hdr)->err;
   a.ext_lam = p.ext_h >= 0 ? at<float>(ws, p.L.xlam) : nullptr;
   a.ext_D = p.ext_h >= 0 ? at<float>(ws, p.L.xD) : nullptr;
   a.ext_T = p.ext_T;
+  a.act = !rev && p.act_f ? at<int32_t>(ws, p.L.act) : nullptr;
+  a.act_nx = p.act_nx;
+  a.act_nz = p.act_nz;
   a.bu = p.born ? at<float>(ws, p.L.bu) + p.d.guard : nullptr;
   a.bw = p.born ? at<float>(ws, p.L.bw) : nullptr;
   return a;
@@ -643,41 +644,57 @@ ExtArgs ext_args(const Plan& p, void* ws, int rbatch) {
   e.I = at<float>(ws, p.L.xI);
   e.hmax = p.ext_h;
   e.groups = p.ext_groups;
-  e.step_ctr = nullptr;
-  e.step_mul = 1;
   e.step0 = 0;
   e.count = 0;
   e.err = &at<Header>(ws, p.L.hdr)->err;
   return e;
 }
 
-hipError_t get_capture_stream(hipStream_t* out) {
-  if (!g_capture_stream) {
-    hipError_t e = hipStreamCreateWithFlags(&g_capture_stream, hipStreamNonBlocking);
-    if (e != hipSuccess) return e;
-  }
-  *out = g_capture_stream;
-  return hipSuccess;
-}
+// Streams and events of the launch chains beside the caller's stream.  A call
+// takes a set for as long as it enqueues and gives it back; a set is reused by
+// later calls (a wait holds the state its event had when the wait was
+// enqueued), and there are as many as calls have enqueued at once per device.
+struct ChainSet {
+  int device = 0;
+  hipStream_t stream[kMaxBranches] = {};
+  hipEvent_t fork = nullptr, join[kMaxBranches] = {};
+};
+std::mutex g_chain_mutex;
+std::vector<std::unique_ptr<ChainSet>> g_chain_pool;
 
-// streams 1 .. n-1 for the branches of a captured chunk, and the events
-hipError_t get_branch_streams(int n) {
-  if (!g_fork) {
-    hipError_t e = hipEventCreateWithFlags(&g_fork, hipEventDisableTiming);
+struct Chains {
+  std::unique_ptr<ChainSet> set;
+  ~Chains() {
+    if (!set) return;
+    std::lock_guard<std::mutex> lock(g_chain_mutex);
+    g_chain_pool.push_back(std::move(set));
+  }
+  // a set of the current device with n - 1 streams
+  hipError_t take(int n) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-  }
-  for (int i = 1; i < n; ++i) {
-    if (!g_branch_stream[i]) {
-      hipError_t e = hipStreamCreateWithFlags(&g_branch_stream[i], hipStreamNonBlocking);
-      if (e != hipSuccess) return e;
+    {
+      std::lock_guard<std::mutex> lock(g_chain_mutex);
+      for (auto it = g_chain_pool.begin(); it != g_chain_pool.end(); ++it)
+        if ((*it)->device == dev) {
+          set = std::move(*it);
+          g_chain_pool.erase(it);
+          break;
+        }
     }
-    if (!g_join[i]) {
-      hipError_t e = hipEventCreateWithFlags(&g_join[i], hipEventDisableTiming);
-      if (e != hipSuccess) return e;
+    if (!set) {
+      set = std::make_unique<ChainSet>();
+      set->device = dev;
     }
+    if (!set->fork && (e = hipEventCreateWithFlags(&set->fork, hipEventDisableTiming)) != hipSuccess) return e;
+    for (int i = 1; i < n; ++i) {
+      if (!set->stream[i] && (e = hipStreamCreateWithFlags(&set->stream[i], hipStreamNonBlocking)) != hipSuccess) return e;
+      if (!set->join[i] && (e = hipEventCreateWithFlags(&set->join[i], hipEventDisableTiming)) != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
-  return hipSuccess;
-}
+};
 
 // slots s0 .. s0 + n - 1 of a launch as a launch of their own (the per-slot
 // arrays of the reverse sweep move with them)
@@ -694,9 +711,7 @@ StepArgs slot_range(const StepArgs& a, int s0, int n) {
   return b;
 }
 
-// Run `nsteps` time steps of one phase for one batch: direct launches, or
-// replays of a captured chunk of `graph_steps` launches that read the step
-// base from the workspace header.
+// Run `nsteps` time steps of one phase for one batch.
 int run_steps(Plan& p, void* ws, int batch, int phase, int flags, int nsteps, const float* wavelet,
               int64_t wstride, hipStream_t stream) {
   if (nsteps <= 0) return FWI_OK;
@@ -722,7 +737,7 @@ int run_steps(Plan& p, void* ws, int batch, int phase, int flags, int nsteps, co
   // the plain reverse sweep of a two-step plan, or the gradient's forward
   // sweep of one: launches of two steps each
   const bool two_rev = phase == kPhaseRev && (flags & ~kRevExt) == 0 && p.rev_steps == 2;
-  const bool two_fwd = phase == kPhaseFwd && flags == (kFwdRecord | kFwdCkpt) && p.fwd_steps == 2;
+  const bool two_fwd = phase == kPhaseFwd && p.fwd_steps == 2;
   const bool two = two_rev || two_fwd;
   const int total_steps = nsteps;  // time steps (the extended image counts these)
   if (two) nsteps = (nsteps + 1) / 2;
@@ -733,126 +748,78 @@ int run_steps(Plan& p, void* ws, int batch, int phase, int flags, int nsteps, co
   if (ext && p.ext_h < 0) return fail(FWI_ERR_STATE, "extended image without its buffers");
   ExtArgs e = ext ? ext_args(p, ws, batch) : ExtArgs{};
   const int spl = two ? 2 : 1;  // time steps per launch
-  e.step_mul = spl;
+  // whether a shot of the reverse batch restarts on the second step of launch q
+  auto reset_b = [&](int q) {
+    for (int i = 0; i < p.Sr; ++i) {
+      const SlotInfo si = p.rslots[(size_t)batch * p.Sr + i];
+      if (si.shot < 0) continue;
+      const ShotDesc& sd = p.shots[si.shot];
+      const int m = sd.nt - 1 - 2 * q, rem = sd.nt - m;
+      if (m >= 2 && rem % sd.K == 0 && rem / sd.K <= sd.nsnap) return true;
+    }
+    return false;
+  };
   auto launch = [&](const StepArgs& args, hipStream_t s) -> hipError_t {
-    if (two_rev) return launch_reverse2(args, p.pf_rev, flags, s);
-    if (two_fwd) return launch_forward2(args, p.pf_fwd == 1 ? 1 : 3, s);
+    if (two_rev) return launch_reverse2(args, p.pf_rev, flags | (reset_b(args.step) ? kRevResetB : 0), s);
+    if (two_fwd) return launch_forward2(args, flags, p.pf_fwd == 1 ? 1 : 3, s);
     return phase == kPhaseFwd ? launch_forward(args, flags, p.pf_fwd, s)
                               : launch_reverse(args, p.pf_rev, flags, s);
   };
-  const int T = p.graph_steps;
-  // fold the ring after the launch that completes a window of ext_T steps,
-  // or the sweep; `done` time steps so far
-  auto fold_direct = [&](int k) -> hipError_t {
-    const int done = std::min(spl * (k + 1), total_steps);
-    if (!(done % p.ext_T == 0 || k == nsteps - 1)) return hipSuccess;
-    e.step_ctr = nullptr;
-    e.step0 = (done - 1) - (done - 1) % p.ext_T;
-    e.count = done - e.step0;
-    return launch_ext_image(e, stream);
+  // Launches of the two-step sweeps as independent chains over shares of the
+  // slots, each on a stream of its own between a fork and a join, so that one
+  // chain's launches fill the others' tails.  One chain where the caller asks
+  // for none (graph_steps = -1) or captures the call.
+  int nbr = two && p.graph_steps > 0 ? std::max(1, std::min({p.branches, a.S, kMaxBranches})) : 1;
+  if (nbr > 1) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) nbr = 1;
+  }
+  Chains chains;
+  StepArgs ab[kMaxBranches];
+  hipStream_t sb[kMaxBranches] = {stream};
+  if (nbr > 1) HIP_TRY(chains.take(nbr));
+  for (int i = 0; i < nbr; ++i) {
+    const int s0 = a.S * i / nbr, s1 = a.S * (i + 1) / nbr;
+    ab[i] = nbr > 1 ? slot_range(a, s0, s1 - s0) : a;
+    if (i) sb[i] = chains.set->stream[i];
+  }
+  auto fork = [&]() -> hipError_t {
+    if (nbr == 1) return hipSuccess;
+    hipError_t e = hipEventRecord(chains.set->fork, stream);
+    for (int i = 1; i < nbr && e == hipSuccess; ++i) e = hipStreamWaitEvent(sb[i], chains.set->fork, 0);
+    return e;
   };
-  if (T <= 0) {
-    for (int k = 0; k < nsteps; ++k) {
-      a.step = k;
-      HIP_TRY(launch(a, stream));
-      if (ext) HIP_TRY(fold_direct(k));
+  // (also after a failed launch: the caller's stream waits for what runs)
+  auto join = [&]() -> hipError_t {
+    hipError_t e = hipSuccess;
+    for (int i = 1; i < nbr; ++i) {
+      hipError_t je = hipEventRecord(chains.set->join[i], sb[i]);
+      if (je == hipSuccess) je = hipStreamWaitEvent(stream, chains.set->join[i], 0);
+      if (e == hipSuccess) e = je;
     }
-    return FWI_OK;
-  }
-  if (ext && p.ext_T != T * spl) return fail(FWI_ERR_STATE, "extended-image ring differs from the graph chunk");
-  int32_t* ctr = &at<Header>(ws, p.L.hdr)->step;
-  // chunks of the two-step sweeps as `branches` independent chains over
-  // shares of the slots, so that one chain's launches fill the others' tails
-  // (the one-step sweeps' chunks stay one chain)
-  const int nbr = two ? std::max(1, std::min({p.branches, a.S, kMaxBranches})) : 1;
-  const std::vector<uint64_t> gkey = {(uint64_t)phase, (uint64_t)flags, (uint64_t)batch, (uint64_t)T, (uint64_t)nbr,
-                                      (uint64_t)(phase == kPhaseFwd ? p.pf_fwd : p.pf_rev),
-                                      (uint64_t)(uintptr_t)ws, (uint64_t)(uintptr_t)wavelet,
-                                      (uint64_t)wstride, (uint64_t)ext, (uint64_t)two};
-  hipGraphExec_t exec = nullptr;
-  // the capture streams, the fork and join events and the plan's graph cache
-  // are shared by calls from every thread
-  std::unique_lock<std::mutex> capture_lock(g_capture_mutex);
-  auto it = p.graphs.find(gkey);
-  if (it != p.graphs.end()) {
-    exec = it->second;
-  } else {
-    hipStream_t cs;
-    HIP_TRY(get_capture_stream(&cs));
-    if (nbr > 1) HIP_TRY(get_branch_streams(nbr));
-    HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
-    a.step_ctr = ctr;
-    hipError_t le = hipSuccess;
-    if (nbr > 1) {
-      // independent chains over consecutive ranges of the slots
-      StepArgs ab[kMaxBranches];
-      hipStream_t sb[kMaxBranches] = {cs};
-      for (int i = 0; i < nbr; ++i) {
-        const int s0 = a.S * i / nbr, s1 = a.S * (i + 1) / nbr;
-        ab[i] = slot_range(a, s0, s1 - s0);
-        if (i) sb[i] = g_branch_stream[i];
-      }
-      le = hipEventRecord(g_fork, cs);
-      int forked = 1;  // streams that are part of the capture
-      while (le == hipSuccess && forked < nbr) {
-        le = hipStreamWaitEvent(sb[forked], g_fork, 0);
-        if (le == hipSuccess) ++forked;
-      }
-      for (int k = 0; k < T && le == hipSuccess; ++k)
-        for (int i = 0; i < nbr && le == hipSuccess; ++i) {
-          ab[i].step = k;
-          le = launch(ab[i], sb[i]);
-        }
-      for (int i = 1; i < forked; ++i) {
-        hipError_t je = hipEventRecord(g_join[i], sb[i]);
-        if (je == hipSuccess) je = hipStreamWaitEvent(cs, g_join[i], 0);
-        if (le == hipSuccess) le = je;
-      }
-    } else {
-      for (int k = 0; k < T && le == hipSuccess; ++k) {
-        a.step = k;
-        le = launch(a, cs);
-      }
+    return e;
+  };
+  HIP_TRY(fork());
+  hipError_t le = hipSuccess;
+  for (int k = 0; k < nsteps && le == hipSuccess; ++k) {
+    for (int i = 0; i < nbr && le == hipSuccess; ++i) {
+      ab[i].step = k;
+      le = launch(ab[i], sb[i]);
     }
-    if (ext && le == hipSuccess) {
-      ExtArgs ec = e;
-      ec.step_ctr = ctr;
-      ec.step0 = 0;
-      ec.count = T * spl;
-      le = launch_ext_image(ec, cs);
+    const int done = std::min(spl * (k + 1), total_steps);
+    if (ext && le == hipSuccess && (done % p.ext_T == 0 || k == nsteps - 1)) {
+      // fold the ring after the launch that completes a window of ext_T
+      // steps, or the sweep
+      e.step0 = (done - 1) - (done - 1) % p.ext_T;
+      e.count = done - e.step0;
+      le = join();
+      if (le == hipSuccess) le = launch_ext_image(e, stream);
+      if (le == hipSuccess && k + 1 < nsteps) le = fork();
     }
-    if (le == hipSuccess) le = launch_advance(ctr, T, cs);
-    hipGraph_t graph = nullptr;
-    hipError_t ee = hipStreamEndCapture(cs, &graph);
-    if (le != hipSuccess) {
-      if (graph) hipGraphDestroy(graph);
-      return fail(FWI_ERR_HIP, std::string("graph capture: ") + hipGetErrorString(le));
-    }
-    if (ee != hipSuccess) return fail(FWI_ERR_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(ee));
-    hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    hipGraphDestroy(graph);
-    if (ie != hipSuccess) return fail(FWI_ERR_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
-    p.graphs[gkey] = exec;
   }
-  capture_lock.unlock();
-  // whole chunks as graph replays, the remainder as direct launches, so that
-  // every launch advances at least one shot
-  const int full = nsteps / T;
-  if (full > 0) {
-    HIP_TRY(launch_set(ctr, 0, stream));
-    for (int c = 0; c < full; ++c) HIP_TRY(hipGraphLaunch(exec, stream));
-  }
-  a.step_ctr = nullptr;
-  for (int k = full * T; k < nsteps; ++k) {
-    a.step = k;
-    HIP_TRY(launch(a, stream));
-  }
-  if (ext && nsteps > full * T) {  // the remaining time steps, one window
-    e.step_ctr = nullptr;
-    e.step0 = full * T * spl;
-    e.count = total_steps - e.step0;
-    HIP_TRY(launch_ext_image(e, stream));
-  }
+  const hipError_t je = join();
+  if (le == hipSuccess) le = je;
+  if (le != hipSuccess) return fail(FWI_ERR_HIP, std::string("sweep: ") + hipGetErrorString(le));
   return FWI_OK;
 }
 
@@ -891,6 +858,7 @@ int begin_call(const Plan& p, void* ws, const float* v, hipStream_t s, const flo
   HIP_TRY(launch_set(&hd->err, 0, s));
   const float vmax = (float)(FWI_CFL_LIMIT * p.dx / p.dt);  // device check in FP32
   HIP_TRY(launch_prep(p.d, v, at<float>(ws, p.L.w), p.dt, p.dx, vmax, &hd->err, s));
+  if (p.act_f) HIP_TRY(launch_fill(at<float>(ws, p.L.traces), sizeof(float) * (size_t)p.nt_max * std::max(p.ntrace, 1), s));
   if (p.born && dv) HIP_TRY(launch_prep_born(p.d, v, dv, at<float>(ws, p.L.bw), s));
   return FWI_OK;
 }
@@ -900,12 +868,22 @@ int forward_batch(Plan& p, void* ws, int b, int flags, const float* wavelet, int
   const SlotInfo* slots = at<SlotInfo>(ws, p.L.slots) + (size_t)b * p.S;
   HIP_TRY(launch_fill_slots(at<float>(ws, p.L.u), p.ulevels * p.d.field, p.ulevels * p.d.field + p.d.guard, slots,
                             p.S, 1, s));
+  if (p.act_f) {
+    // what skipped tiles leave unwritten
+    HIP_TRY(launch_act_reset(at<int32_t>(ws, p.L.act), (int64_t)p.act_nx * p.act_nz, slots, p.S, s));
+    if (flags & kFwdCkpt) {
+      HIP_TRY(launch_fill_slots(at<float>(ws, p.L.strip), p.strip_stride, (int64_t)p.batch_nt[b] * p.d.ring, slots, p.S,
+                                1, s));
+      HIP_TRY(launch_fill_slots(at<float>(ws, p.L.snap), p.snap_stride, p.snap_stride, slots, p.S, 1, s));
+    }
+    if (flags & kFwdIllum) HIP_TRY(launch_fill(at<float>(ws, p.L.E), sizeof(float) * p.d.model * p.S, s));
+  }
   if (flags & kFwdBorn)
     HIP_TRY(launch_fill_slots(at<float>(ws, p.L.bu), p.blevels * p.d.field, p.blevels * p.d.field + p.d.guard, slots,
                               p.S, 1, s));
   if (int rc = run_steps(p, ws, b, kPhaseFwd, flags, p.batch_nt[b] - 1, wavelet, wstride, s)) return rc;
   // the reverse sweep starts from the first set of levels
-  const int spl = p.bf.T ? p.bf.T : (flags == (kFwdRecord | kFwdCkpt) ? p.fwd_steps : 1);
+  const int spl = p.bf.T ? p.bf.T : p.fwd_steps;
   if ((flags & kFwdCkpt) && spl > 1)
     HIP_TRY(launch_forward2_finish(at<float>(ws, p.L.u) + p.d.guard, p.ulevels * p.d.field, kULevels * p.d.field,
                                    slots, at<ShotDesc>(ws, p.L.shots), p.S, spl, s));
@@ -1029,9 +1007,9 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   // (not the Born one), tried first so that near-ties keep the fewer bytes
   std::vector<int> FSs;
   if (ex && ex->forward_steps > 0) FSs = {ex->forward_steps};
-  else if (g->free_surface || !(what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE))
-    FSs = {1};
+  else if (g->free_surface || what == FWI_WS_BORN || what == FWI_WS_GNHVP) FSs = {1};
   else FSs = {2, 1};
+  if (!grad && ex && ex->forward_steps > 0) FSs = {1};  // (the field is the gradient's)
   const int fwd_flags = grad ? (kFwdRecord | kFwdCkpt) : (what == FWI_WS_HESSIAN ? kFwdIllum : kFwdRecord);
   const int nsteps = 32;  // launches timed per candidate
   // FWI_TUNE_LOG set: each candidate's best time goes to stderr
@@ -1041,8 +1019,7 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   // graph replays in launch chains they run as in a sweep, not as direct
   // launches), to keep the choice stable
   auto timed = [&](Plan& p, int flags, int phase) {
-    const bool two = phase == kPhaseRev ? (flags == 0 && p.rev_steps == 2)
-                                        : (flags == (kFwdRecord | kFwdCkpt) && p.fwd_steps == 2);
+    const bool two = phase == kPhaseRev ? (flags == 0 && p.rev_steps == 2) : p.fwd_steps == 2;
     const int n = two ? 2 * nsteps : nsteps;
     return std::min(time_steps(p, ws, flags, phase, n, wavelet, wstride, s),
                     time_steps(p, ws, flags, phase, n, wavelet, wstride, s)) / n;
@@ -1068,8 +1045,10 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
       // sweep has twice the wavefield levels)
       auto prepare = [&](int fs) -> std::shared_ptr<Plan> {
         ExecChoice c{S, TZ, best.graph_steps, PFs[0], RFs[0], S, TZ, rs_max, fs, best.branches};
+        c.even_k = rs_max == 2;
         auto p = build_plan(g, geo, c, 0, what, 0);
         if (p->L.total > ws_bytes) return nullptr;
+        p->act_f = false;  // the first steps reach few tiles: time whole launches
         if (begin_call(*p, ws, v, s) != FWI_OK) return nullptr;
         if (launch_fill(at<char>(ws, p->L.u), p->L.g - p->L.u, s) != hipSuccess) return nullptr;
         return p;
@@ -1129,12 +1108,15 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
     if (x.S != y.S) return x.S > y.S;
     return x.TZ > y.TZ;
   });
-  // the same for the forward: two steps per launch, more shots, then longer
-  // bands (fewer halo rows read twice)
+  // the same for the forward: two steps per launch, more shots, then shorter
+  // bands: the timings run every tile, a sweep only those that the wavefield
+  // has reached, which short bands follow closer (1024 x 384, 32 shots of 4000
+  // steps: whole launches take the same time with 16 and 32 rows, the sweeps
+  // 128 and 143 ms)
   std::stable_sort(F.begin(), F.end(), [](const Cand& x, const Cand& y) {
     if (x.fs != y.fs) return x.fs > y.fs;
     if (x.S != y.S) return x.S > y.S;
-    return x.TZ > y.TZ;
+    return x.fs == 2 ? x.TZ < y.TZ : x.TZ > y.TZ;
   });
   // per forward shots-in-flight value, the forward settings and the reverse
   // settings (shots in flight dividing the forward's; any size in the
@@ -1156,7 +1138,7 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
     if (!grad) {
       if (fb->per_shot < best_t * 0.98) {
         best_t = fb->per_shot;
-        choice = ExecChoice{fb->S, fb->TZ, best.graph_steps, fb->pf, best.pf_rev, fb->S, fb->TZ, 1, 1};
+        choice = ExecChoice{fb->S, fb->TZ, best.graph_steps, fb->pf, best.pf_rev, fb->S, fb->TZ, 1, fb->fs};
       }
       continue;
     }
@@ -1208,6 +1190,34 @@ ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exe
   c.branches = (ex && ex->graph_branches > 0) ? ex->graph_branches : kDefaultBranches;
   c.blk = blk_allowed(ex);
   return c;
+}
+
+// The settings of an untuned call that names no z-sweep field: the
+// LDS-resident sweeps up to the sizes of blk_tiling(), two steps per launch
+// above them, with the tile rows that ran fastest there (us per step, rows 16 /
+// 32 / 64; forward 3.9 M cells a step 19.4 / 26.2 / 39.9, 7.8 M 25.2 / 32.3 /
+// 44.8, 15.6 M 45.4 / 45.2 / 58.3; reverse 30.2 / 39.7 / 61.1 (8 rows: 28.9),
+// 47.0 / 51.7 / 70.0, 92.2 / 87.7 / 97.9; one step per launch with 64 rows: 95 us forward at
+// 15.6 M).
+void untuned_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, ExecChoice& c) {
+  const int autos = blk_allowed(ex);
+  if (!autos || g->free_surface || geo->nshot == 0) return;
+  const int runs = std::max(1, std::min(c.S, geo->nshot));
+  const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
+  int most_recv = 0;
+  for (int s = 0; s < geo->nshot; ++s) most_recv = std::max(most_recv, geo->rec_ptr[s + 1] - geo->rec_ptr[s]);
+  const bool blk = g->nsponge <= kBlkSponge && most_recv <= kBlkRecv;
+  if ((autos & 1) && what != FWI_WS_BORN && what != FWI_WS_GNHVP && !(blk && cells <= kBlkFwdCells)) {
+    c.fsteps = 2;
+    c.pf_fwd = 1;
+    if (!c.TZr) c.TZr = c.TZ;
+    c.TZ = cells < 12000000 ? 16 : 32;
+  }
+  if ((autos & 2) && what != FWI_WS_FORWARD && what != FWI_WS_HESSIAN && what != FWI_WS_BORN &&
+      !(blk && cells <= kBlkRevCells)) {
+    c.rsteps = 2;
+    c.TZr = cells < 5000000 ? 8 : cells < 12000000 ? 16 : cells < 24000000 ? 32 : 64;
+  }
 }
 
 std::vector<uint64_t> tune_key(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what) {
@@ -1332,6 +1342,7 @@ uint64_t plan_key(uint64_t ikey, int what, int plain, const ExecChoice& c, int e
   h.pod(c.rsteps);
   h.pod(c.fsteps);
   h.pod(c.branches);
+  h.pod(c.even_k);
   h.pod(c.blk);
   h.pod(ext_h);
   return h.h;
@@ -1381,23 +1392,39 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
     }
   }
   c.branches = branches;
-  c.blk = compact ? 0 : blk;
-  if (c.blk && !plain && ex && ex->autotune && !(ex->shots_in_flight > 0)) {
-    // the tuned shots in flight are the z sweeps': whether the LDS-resident
-    // ones take over is decided for every shot at once, which suits them best
-    const int runs = std::min(std::max(geo->nshot, 1), 64);
-    const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
-    const bool rev = what != FWI_WS_FORWARD && what != FWI_WS_HESSIAN && what != FWI_WS_BORN;
-    if (cells > kBlkFwdCells) c.blk &= ~1;
-    if (cells > kBlkRevCells) c.blk &= ~2;
-    if (c.blk & 1) c.fsteps = 1;
-    if (c.blk & 2) c.rsteps = 1;
-    if (c.blk == 3 || (c.blk && !rev)) {
-      c.S = runs;
-      c.Sr = 0;
+  // Two steps per launch by request or tuning come with an even snapshot
+  // spacing, whatever form then runs the sweep: the reconstruction's rounding
+  // (1e-5 of the gradient over 4000 steps) depends on where it restarts.
+  // Tuned calls are sized for the spacing that keeps more.
+  c.even_k = c.rsteps == 2 && !plain && !g->free_surface && !(sizing_only && !compact && ex && ex->autotune);
+  const ExecChoice tuned = c;
+  const bool forward_only = what == FWI_WS_FORWARD || what == FWI_WS_HESSIAN || what == FWI_WS_BORN;
+  // compact: what a workspace of the one-step z sweeps' (tuned calls: the z
+  // sweeps') size holds
+  auto settle = [&](bool small) {
+    c = tuned;
+    c.blk = small ? 0 : blk;
+    if (small && forward_only) c.fsteps = 1;
+    if (plain || small) return;
+    if (!(ex && ex->autotune)) {
+      untuned_choice(g, geo, ex, what, c);
+    } else if (c.blk && !(ex->shots_in_flight > 0)) {
+      // the tuned shots in flight are the z sweeps': whether the LDS-resident
+      // ones take over is decided for every shot at once, which suits them best
+      const int runs = std::min(std::max(geo->nshot, 1), 64);
+      const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
+      if (cells > kBlkFwdCells) c.blk &= ~1;
+      if (cells > kBlkRevCells) c.blk &= ~2;
+      if (c.blk & 1) c.fsteps = 1;
+      if (c.blk & 2) c.rsteps = 1;
+      if (c.blk == 3 || (c.blk && forward_only)) {
+        c.S = runs;
+        c.Sr = 0;
+      }
     }
-  }
-  auto find_or_build = [&](uint64_t key) {
+  };
+  auto find_or_build = [&]() {
+    const uint64_t key = plan_key(ikey, what, plain, c, ext_h);
     for (auto it = g_plans.begin(); it != g_plans.end(); ++it) {
       if ((*it)->key == key) {
         out = *it;
@@ -1412,11 +1439,11 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
       while (g_plans.size() > 16) g_plans.pop_back();
     }
   };
-  find_or_build(plan_key(ikey, what, plain, c, ext_h));
-  if (!sizing_only && c.blk && out->L.total > ws_bytes) {
-    // a workspace of the z sweeps' size: run those
-    c.blk = 0;
-    find_or_build(plan_key(ikey, what, plain, c, ext_h));
+  settle(compact);
+  find_or_build();
+  if (!sizing_only && out->L.total > ws_bytes) {
+    settle(true);
+    find_or_build();
   }
   return FWI_OK;
 }
@@ -1552,6 +1579,11 @@ ExecChoice dx_choice(const fwi_grid* g, const fwi_exec* ex, int S, bool compact)
   // direct launches: the capture pointer is not baked into any graph
   ExecChoice c{S, TZ, 0, pf, 1, S, TZ, 1, 1};
   c.blk = compact ? 0 : blk_allowed(ex) & 1;
+  const int64_t cells = (int64_t)S * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
+  if (c.blk && (cells > kBlkFwdCells || g->nsponge > kBlkSponge)) {
+    c.fsteps = 2;  // two steps per launch, rows as in untuned_choice()
+    c.TZ = cells < 12000000 ? 16 : 32;
+  }
   return c;
 }
 
@@ -1659,6 +1691,7 @@ int fwi_exec_query(const fwi_grid* grid, const fwi_geometry* geom, const fwi_exe
     return fail(FWI_ERR_ARG, "bad `what`");
   const int plain = exec && exec->mode == FWI_EXEC_PLAIN;
   ExecChoice c = base_choice(grid, geom, exec);
+  if (!plain && !(exec && exec->autotune)) untuned_choice(grid, geom, exec, what, c);
   if (!plain && exec && exec->autotune) {
     std::lock_guard<std::mutex> lock(g_mutex);
     const std::vector<uint64_t> tk = tune_key(grid, geom, exec, what);
@@ -2049,7 +2082,10 @@ int fwi_offset_diag_exact(const fwi_grid* grid, const fwi_geometry* geom, const 
         const SlotInfo* slots = at<SlotInfo>(workspace, p->L.slots) + (size_t)b * p->S;
         HIP_TRY(launch_fill_slots(at<float>(workspace, p->L.u), p->ulevels * p->d.field,
                                   p->ulevels * p->d.field + p->d.guard, slots, p->S, 1, s));
-        StepArgs a = step_args(*p, workspace, b, kPhaseFwd, rcv ? imp : wsrc, rcv ? 0 : wst, false);
+        const bool two = p->fwd_steps == 2;
+        if (p->act_f)
+          HIP_TRY(launch_act_reset(at<int32_t>(workspace, p->L.act), (int64_t)p->act_nx * p->act_nz, slots, p->S, s));
+        StepArgs a = step_args(*p, workspace, b, kPhaseFwd, rcv ? imp : wsrc, rcv ? 0 : wst, two);
         a.cap = cap;
         a.cap_T = o.Tc;
         a.cap_R = o.R;
@@ -2063,6 +2099,11 @@ int fwi_offset_diag_exact(const fwi_grid* grid, const fwi_geometry* geom, const 
             for (int k = k0 / ba.T; k * ba.T < k0 + tc; ++k) {
               ba.s.step = k;
               HIP_TRY(launch_forward_block(ba, flags, s));
+            }
+          } else if (two) {
+            for (int k = k0 / 2; 2 * k < k0 + tc; ++k) {
+              a.step = k;
+              HIP_TRY(launch_forward2(a, flags, p->pf_fwd == 1 ? 1 : 3, s));
             }
           } else {
             for (int k = k0; k < k0 + tc; ++k) {
