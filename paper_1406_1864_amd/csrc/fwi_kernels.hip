@@ -1382,17 +1382,22 @@ __global__ __launch_bounds__(256) void k_ext_image(ExtArgs a) {
 
 // Four columns per lane: each lane keeps the 2HM+1 sums of 4 adjacent
 // columns, reads its 4 + 2HM operands of lam and D per step as float4 rows
-// from LDS (one read per operand serves up to four products instead of one),
-// and the next step's rows are loaded while the current one is folded.  The
+// from LDS (one read per operand serves up to four products instead of one).
+// Two wavefronts per SIMD hold the sums, too few to cover the latency of the
+// rows' loads: the rows of the next kExtAhead steps are on their way while one
+// is folded, and the sums of four columns go to the image as one float4.  All
+// 2HM+1 offsets of the instance are summed (a test per offset cost more than
+// the sums it saved).  A window of 32 steps of 4 slots at 1024 x 384, |h| <= 16:
+// 433 -> 184 us; its 0.8 GB of operands and partial images take 160 us.  The
 // slots are split into `groups` so that enough wavefronts run; each group
 // adds into its own partial image.
+constexpr int kExtAhead = 4;
 template <int HM>
 __global__ __launch_bounds__(256) void k_ext_image4(ExtArgs a) {
   constexpr int C = 4;
   constexpr int TW = kWave * C;           // columns per wavefront
   constexpr int L = TW + 2 * HM;          // staged row length
   constexpr int NL = (L + kWave - 1) / kWave;
-  constexpr int WIN = C + 2 * HM;         // operands one lane reads
   static_assert(HM % 4 == 0, "window reads are float4");
   __shared__ __align__(16) float shL_all[kWavesPerBlock][L];
   __shared__ __align__(16) float shD_all[kWavesPerBlock][L];
@@ -1417,10 +1422,10 @@ __global__ __launch_bounds__(256) void k_ext_image4(ExtArgs a) {
   for (int c = 0; c < C; ++c)
 #pragma unroll
     for (int h = 0; h < 2 * HM + 1; ++h) acc[c][h] = 0.0f;
-  float nl[NL], nd[NL];
+  float nl[kExtAhead][NL], nd[kExtAhead][NL];
   // loads of iteration `it` = (slot s_lo + it / count, step it % count); a
   // slot whose shot has ended contributes zeros
-  auto issue = [&](int it) {
+  auto issue = [&](int it, float(&l)[NL], float(&dd)[NL]) __attribute__((always_inline)) {
     const int s = s_lo + it / a.count, j = j0 + it % a.count;
     const SlotInfo si = a.slots[s];
     const bool ok = si.shot >= 0 && a.shots[si.shot].nt - 1 - j >= 1;
@@ -1430,48 +1435,83 @@ __global__ __launch_bounds__(256) void k_ext_image4(ExtArgs a) {
       const int c = lane + kWave * q;
       const int xx = x0 - HM + c;
       const bool in = ok && c < L && xx >= 0 && xx < d.nx;
-      nl[q] = in ? a.lam[row + xx] : 0.0f;
-      nd[q] = in ? a.D[row + xx] : 0.0f;
+      l[q] = in ? a.lam[row + xx] : 0.0f;
+      dd[q] = in ? a.D[row + xx] : 0.0f;
     }
   };
-  if (n_it > 0) issue(0);
-  for (int it = 0; it < n_it; ++it) {
+  auto fold = [&]() __attribute__((always_inline)) {
+    // column x0 + C lane + c, offset h: lam at window index c + HM - h, D at
+    // c + HM + h; four offsets at a time, so that two float4 of each operand
+    // are live instead of both windows
+    const float4* wl = reinterpret_cast<const float4*>(shL + C * lane);
+    const float4* wd = reinterpret_cast<const float4*>(shD + C * lane);
+    float lw[2 * C], dw[2 * C];
+    auto put = [](float* w, float4 t) __attribute__((always_inline)) {
+      w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+    };
+    put(lw + C, wl[2 * HM / 4]);
+    put(dw, wd[0]);
 #pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const int c = lane + kWave * q;
-      if (c < L) {
-        shL[c] = nl[q];
-        shD[c] = nd[q];
+    for (int b = 0; b <= 2 * HM / 4; ++b) {
+      const bool last = b == 2 * HM / 4;  // h = HM alone
+      if (!last) {
+        put(lw, wl[2 * HM / 4 - 1 - b]);
+        put(dw + C, wd[b + 1]);
       }
+#pragma unroll
+      for (int r = 0; r < (last ? 1 : 4); ++r)
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[c][4 * b + r] = fmaf(lw[C + c - r], dw[c + r], acc[c][4 * b + r]);
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        lw[C + c] = lw[c];
+        dw[c] = dw[C + c];
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (it + 1 < n_it) issue(it + 1);
     wave_lds_fence();
-    float lw[WIN], dw[WIN];
+  };
 #pragma unroll
-    for (int k = 0; k < WIN / 4; ++k) {
-      const float4 tl = *reinterpret_cast<const float4*>(shL + C * lane + 4 * k);
-      const float4 td = *reinterpret_cast<const float4*>(shD + C * lane + 4 * k);
-      lw[4 * k] = tl.x; lw[4 * k + 1] = tl.y; lw[4 * k + 2] = tl.z; lw[4 * k + 3] = tl.w;
-      dw[4 * k] = td.x; dw[4 * k + 1] = td.y; dw[4 * k + 2] = td.z; dw[4 * k + 3] = td.w;
+  for (int p = 0; p < kExtAhead; ++p)
+    if (p < n_it) issue(p, nl[p], nd[p]);
+  for (int it = 0; it < n_it; it += kExtAhead) {
+#pragma unroll
+    for (int p = 0; p < kExtAhead; ++p) {
+      if (it + p >= n_it) break;
+#pragma unroll
+      for (int q = 0; q < NL; ++q) {
+        const int c = lane + kWave * q;
+        if (c < L) {
+          shL[c] = nl[p][q];
+          shD[c] = nd[p][q];
+        }
+      }
+      if (it + p + kExtAhead < n_it) issue(it + p + kExtAhead, nl[p], nd[p]);
+      wave_lds_fence();
+      fold();
     }
-    // column x0 + C lane + c, offset h: lam at window index c + HM - h, D at c + HM + h
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-#pragma unroll
-      for (int h = -HM; h <= HM; ++h)
-        if (h >= -H && h <= H) acc[c][h + HM] = fmaf(lw[c + HM - h], dw[c + HM + h], acc[c][h + HM]);
-    wave_lds_fence();
   }
   float* I = a.I + (int64_t)grp * (2 * H + 1) * d.model;
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const int x = x0 + C * lane + c;
-    if (x >= d.nx) continue;
-    const int64_t cell = (int64_t)iz * d.nx + x;
+  const int x = x0 + C * lane;
+  if (x >= d.nx) return;
+  float* cell = I + (int64_t)iz * d.nx + x;
+  if (d.nx % C == 0 && reinterpret_cast<uintptr_t>(a.I) % 16 == 0) {  // then every row of every offset is aligned
 #pragma unroll
     for (int h = -HM; h <= HM; ++h)
-      if (h >= -H && h <= H) I[(int64_t)(h + H) * d.model + cell] += acc[c][h + HM];
+      if (h >= -H && h <= H) {
+        float4* q = reinterpret_cast<float4*>(cell + (int64_t)(h + H) * d.model);
+        float4 t = *q;
+        t.x += acc[0][h + HM]; t.y += acc[1][h + HM]; t.z += acc[2][h + HM]; t.w += acc[3][h + HM];
+        *q = t;
+      }
+    return;
   }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (x + c < d.nx)
+#pragma unroll
+      for (int h = -HM; h <= HM; ++h)
+        if (h >= -H && h <= H) cell[(int64_t)(h + H) * d.model + c] += acc[c][h + HM];
 }
 
 // image(x, h) = (2 / v(x)^3) sum over groups of Iacc[g](x, h), fixed order
