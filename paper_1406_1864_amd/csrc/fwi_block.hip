@@ -125,10 +125,11 @@ struct Patch {
   }
   // sponge table entries of a row's cells (columns past the grid, whose w is
   // 0, take the last one)
-  __device__ __forceinline__ void depths(const Dims& d, int i, int (&dd)[4]) const {
+  template <class T>
+  __device__ __forceinline__ void sponge(const Dims& d, const T* tab, int i, T (&t)[4]) const {
     const int dz = depth_z(d, i);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) dd[j] = min(max(dz, depth_x(d, j)), d.N);
+    for (int j = 0; j < 4; ++j) t[j] = tab[min(max(dz, depth_x(d, j)), d.N)];
   }
   // A copy whose indices and masks are computed where they are used: rare or
   // final accesses, whose addresses would otherwise live in registers over
@@ -271,13 +272,10 @@ __device__ __forceinline__ void sponge_table(Sponge* tab, double sp_a, int N) {
 // correction, which rounds like it.  Four cells at a time, so that their
 // table reads and FP64 chains overlap.
 template <bool SECOND>
-__device__ __forceinline__ void damp_row(const Sponge* tab, const int (&dd)[4], uint32_t model, const float (&c)[4],
+__device__ __forceinline__ void damp_row(const Sponge (&t)[4], uint32_t model, const float (&c)[4],
                                          const float (&old)[4], const float (&w)[4], const float (&lap)[4],
                                          float (&v)[4]) {
-  Sponge t[4];
   double x[4], q[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) t[j] = tab[dd[j]];
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     x[j] = SECOND ? 2.0 * (double)c[j] - t[j].minus * (double)old[j] + (double)w[j] * (double)lap[j]
@@ -417,6 +415,12 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
   }
   lds_barrier();
   const int nrec = REC ? rcount : 0;
+  // One row of cells per thread leaves registers for its table entries, which
+  // the steps of a launch otherwise read again from LDS (24 x 16, 2 shots, 400
+  // steps: 214 -> 188 us, reverse 315 -> 290; 200 x 100: 14.5 -> 13.3 us a launch)
+  constexpr bool REGTAB = PZ == 1 && !BORN;
+  Sponge treg[4];
+  if (REGTAB && sponge) p.sponge(d, tab, 0, treg);
   // u[n+1] is saved where nt-2-n is a positive multiple of K: `save` steps
   // from now, as pair `snap`
   int save = CKPT ? (sd.nt - 2 - n0) % sd.K : 0, snap = CKPT ? (sd.nt - 2 - n0) / sd.K - 1 : 0;
@@ -454,10 +458,11 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
       const PT r = p.here();
 #pragma unroll
       for (int i = 0; i < PZ; ++i) {
-        int dd[4];
-        r.depths(d, i, dd);
-        damp_row<false>(tab, dd, r.model >> (4 * i), dn[i], dn[i], w[i], lap[i], un[i]);
-        if constexpr (BORN) damp_row<false>(tab, dd, r.model >> (4 * i), bd[i], bd[i], w[i], blap[i], bn[i]);
+        Sponge tl[4];
+        if constexpr (!REGTAB) r.sponge(d, tab, i, tl);
+        const Sponge(&t)[4] = REGTAB ? treg : tl;
+        damp_row<false>(t, r.model >> (4 * i), dn[i], dn[i], w[i], lap[i], un[i]);
+        if constexpr (BORN) damp_row<false>(t, r.model >> (4 * i), bd[i], bd[i], w[i], blap[i], bn[i]);
       }
     }
 #pragma unroll
@@ -659,6 +664,9 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_reverse_block(BlockAr
   for (int r = threadIdx.x; r < nrec; r += PT::NT) psi[0][r] = s.traces[(int64_t)m0 * s.ntrace + rtrace[r]];
   lds_barrier();
 
+  constexpr bool REGTAB = PZ == 1 && RZ == 32;
+  Sponge treg[4];
+  if (REGTAB && sponge) p.sponge(d, tab, 0, treg);
   // restarts at nt-1-m = K, 2K, ...: the next one `restart` steps from now,
   // from pair `snap`
   int restart = (sd.K - j0 % sd.K) % sd.K, snap = (j0 + sd.K - 1) / sd.K - 1;
@@ -728,9 +736,10 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_reverse_block(BlockAr
       const PT r = p.here();
 #pragma unroll
       for (int i = 0; i < PZ; ++i) {
-        int dd[4];
-        r.depths(d, i, dd);
-        damp_row<true>(tab, dd, r.model >> (4 * i), lc[i], lp[i], w[i], lap[i], ln[i]);
+        Sponge tl[4];
+        if constexpr (!REGTAB) r.sponge(d, tab, i, tl);
+        const Sponge(&t)[4] = REGTAB ? treg : tl;
+        damp_row<true>(t, r.model >> (4 * i), lc[i], lp[i], w[i], lap[i], ln[i]);
       }
     }
 #pragma unroll
