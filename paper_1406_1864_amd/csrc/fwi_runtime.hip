@@ -1197,26 +1197,31 @@ ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exe
 // above them, with the tile rows that ran fastest there (us per step, rows 16 /
 // 32 / 64; forward 3.9 M cells a step 19.4 / 26.2 / 39.9, 7.8 M 25.2 / 32.3 /
 // 44.8, 15.6 M 45.4 / 45.2 / 58.3; reverse 30.2 / 39.7 / 61.1 (8 rows: 28.9),
-// 47.0 / 51.7 / 70.0, 92.2 / 87.7 / 97.9; one step per launch with 64 rows: 95 us forward at
-// 15.6 M).
+// 47.0 / 51.7 / 70.0, 92.2 / 87.7 / 97.9).  One step per launch where two are
+// not to be had (free surface, Born modelling): 16 rows, 1 row of prefetch (8,
+// 16, 32, 64 rows with 1 | 64 with 3, the former default, at 1024 x 384, 8
+// shots, free surface: forward 20.6, 19.9, 24.8, 37.8 | 61.8 us, reverse 30.5,
+// 31.9, 39.7, 64.3 | 87.6, Born 33.8, 32.9, 46.0, 77.4 | 88.1; 32 shots: 58.7,
+// 51.2, 56.7, 57.7 | 96.1, 119, 120, 128, 131 | 169, 154, 154, 159, 159 | 175).
 void untuned_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, ExecChoice& c) {
   const int autos = blk_allowed(ex);
-  if (!autos || g->free_surface || geo->nshot == 0) return;
+  if (!autos || geo->nshot == 0) return;
   const int runs = std::max(1, std::min(c.S, geo->nshot));
   const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
   int most_recv = 0;
   for (int s = 0; s < geo->nshot; ++s) most_recv = std::max(most_recv, geo->rec_ptr[s + 1] - geo->rec_ptr[s]);
   const bool blk = g->nsponge <= kBlkSponge && most_recv <= kBlkRecv;
-  if ((autos & 1) && what != FWI_WS_BORN && what != FWI_WS_GNHVP && !(blk && cells <= kBlkFwdCells)) {
-    c.fsteps = 2;
+  if ((autos & 1) && !(blk && cells <= kBlkFwdCells)) {
+    const bool two = !g->free_surface && what != FWI_WS_BORN && what != FWI_WS_GNHVP;
+    c.fsteps = two ? 2 : 1;
     c.pf_fwd = 1;
     if (!c.TZr) c.TZr = c.TZ;
-    c.TZ = cells < 12000000 ? 16 : 32;
+    c.TZ = two && cells >= 12000000 ? 32 : 16;
   }
   if ((autos & 2) && what != FWI_WS_FORWARD && what != FWI_WS_HESSIAN && what != FWI_WS_BORN &&
       !(blk && cells <= kBlkRevCells)) {
-    c.rsteps = 2;
-    c.TZr = cells < 5000000 ? 8 : cells < 12000000 ? 16 : cells < 24000000 ? 32 : 64;
+    c.rsteps = g->free_surface ? 1 : 2;
+    c.TZr = cells < 5000000 ? 8 : cells < 12000000 || g->free_surface ? 16 : cells < 24000000 ? 32 : 64;
   }
 }
 
