@@ -317,8 +317,12 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
   using PT = Patch<RX, RZ, PZ>;
   constexpr bool BORN = (FLAGS & kFwdBorn) != 0, CKPT = (FLAGS & kFwdCkpt) != 0, REC = (FLAGS & kFwdRecord) != 0;
   constexpr bool ILLUM = (FLAGS & kFwdIllum) != 0, CAP = (FLAGS & (kFwdCapD | kFwdCapU)) != 0;
-  __shared__ __align__(16) float lu[PT::LF];
-  __shared__ __align__(16) float lb[BORN ? PT::LF : 4];
+  // two fields in turn take one barrier a step instead of two, where LDS is
+  // not what limits the workgroups of a CU
+  constexpr int NB = PZ == 1 || (PZ == 2 && !BORN) ? 2 : 1, SWAP = (NB - 1) * PT::LF;
+  __shared__ __align__(16) float fu[NB * PT::LF];
+  __shared__ __align__(16) float fb[BORN ? NB * PT::LF : 4];
+  float *lu = fu, *lb = fb;
   __shared__ Sponge tab[kBlkSponge + 1];
   __shared__ int rcount, rcell[REC ? kBlkRecv : 1], rtrace[REC ? kBlkRecv : 1];
   __shared__ float wav[kBlkSteps];
@@ -400,8 +404,11 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
   sponge = __any(sponge);  // per wavefront: some cell is not a plain interior one
   const bool image = d.fs && rz0 == d.ztop;
 
-  p.clear_rim(lu);
-  if constexpr (BORN) p.clear_rim(lb);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    p.clear_rim(fu + b * PT::LF);
+    if constexpr (BORN) p.clear_rim(fb + b * PT::LF);
+  }
   sponge_table(tab, s.sp_a, d.N);
   if (threadIdx.x == 0) rcount = 0;
   lds_barrier();
@@ -516,7 +523,9 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
     for (int i = 0; i < PZ; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) uc[i][j] = un[i][j];
-    lds_barrier();  // every read of the step before its writes
+    if constexpr (NB == 1) lds_barrier();  // every read of the step before its writes
+    lu = fu + (k & 1 ? 0 : SWAP);
+    if constexpr (BORN) lb = fb + (k & 1 ? 0 : SWAP);
     p.put(lu, uc);
     if (image) p.put_image(lu, uc);
     if constexpr (BORN) {
@@ -569,8 +578,10 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_forward_block(BlockAr
 template <int RX, int RZ, int PZ, bool EXT, bool IMGU>
 __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_reverse_block(BlockArgs a) {
   using PT = Patch<RX, RZ, PZ>;
-  __shared__ __align__(16) float lu[PT::LF];
-  __shared__ __align__(16) float ll[PT::LF];
+  constexpr int NB = PZ == 1 ? 2 : 1, SWAP = (NB - 1) * PT::LF;  // (as in the forward sweep)
+  __shared__ __align__(16) float fu[NB * PT::LF];
+  __shared__ __align__(16) float fl[NB * PT::LF];
+  float *lu = fu, *ll = fl;
   __shared__ Sponge tab[kBlkSponge + 1];
   __shared__ int rcount, rtrace[kBlkRecv];
   __shared__ __align__(8) uint16_t map[RX * RZ];
@@ -652,8 +663,11 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_reverse_block(BlockAr
   }
   lds_barrier();
   const int nrec = rcount;
-  p.clear_rim(lu);
-  p.clear_rim(ll);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    p.clear_rim(fu + b * PT::LF);
+    p.clear_rim(fl + b * PT::LF);
+  }
   sponge_table(tab, s.sp_a, d.N);
   p.put(lu, uc);
   p.put(ll, lc);
@@ -799,7 +813,9 @@ __global__ __launch_bounds__(RX / 4 * (RZ / PZ), 4) void k_reverse_block(BlockAr
         uc[i][j] = un[i][j];
         lc[i][j] = ln[i][j];
       }
-    lds_barrier();
+    if constexpr (NB == 1) lds_barrier();
+    lu = fu + (k & 1 ? 0 : SWAP);
+    ll = fl + (k & 1 ? 0 : SWAP);
     p.put(lu, uc);
     p.put(ll, lc);
     if (image) {
