@@ -224,7 +224,8 @@ __global__ __launch_bounds__(kThreads) void k_dft(DftArgs a) {
     }
   };
 
-  for (int slot = 0; slot < a.nslots; ++slot) {
+  const int slot_end = min(((int)blockIdx.y + 1) * a.per, a.nslots);
+  for (int slot = blockIdx.y * a.per; slot < slot_end; ++slot) {
     // the first two slabs' loads go out before the running spectra's
     load(s0, slot, 0);
     // the run's spectra, lane row pointer: the wavefront's 16 rows (m, i)
@@ -299,6 +300,28 @@ __global__ __launch_bounds__(kThreads) void k_dft(DftArgs a) {
   }
 }
 
+// P[k][cell] += C[2k][cell]^2 + C[2k+1][cell]^2 of every run in order: the last
+// chunk's epilogue as a pass of its own, where the runs were split over
+// workgroups.  Four cells per thread, bound by the bytes of C.
+__global__ __launch_bounds__(256) void k_dft_power(DftArgs a) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= a.Kp * a.R) return;
+  const int64_t k = i / a.R, cell = i % a.R;
+  float4* const p = (float4*)(a.P + i);
+  float4 sum = *p;
+  const float* row = a.C + 2 * k * a.R + cell;
+#pragma unroll 4
+  for (int slot = 0; slot < a.nslots; ++slot) {
+    const float4 c = *(const float4*)row, q = *(const float4*)(row + a.R);
+    sum.x = fmaf(c.x, c.x, fmaf(q.x, q.x, sum.x));
+    sum.y = fmaf(c.y, c.y, fmaf(q.y, q.y, sum.y));
+    sum.z = fmaf(c.z, c.z, fmaf(q.z, q.z, sum.z));
+    sum.w = fmaf(c.w, c.w, fmaf(q.w, q.w, sum.w));
+    row += (int64_t)a.Cp * a.R;
+  }
+  *p = sum;
+}
+
 // (cos, sin)(2 pi r / L) of the phase r = k t mod L, reduced exactly in
 // integers, the angle in double
 __device__ __forceinline__ float2 phase(int64_t k, int64_t t, int L) {
@@ -332,10 +355,29 @@ hipError_t launch_dft(const DftArgs& a, int split, hipStream_t s) {
     return hipErrorInvalidValue;
   const int64_t blocks = (int64_t)((a.ntile + 7) / 8) * 8 * (a.Cp / kDftCols);
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
+  // A workgroup has a CU to itself and takes its tile's runs one after the
+  // other, which leaves CUs idle where the tiles are few.  `per` runs to a
+  // workgroup take rounds * per runs' time; the runs are split where that is
+  // at most 3/4 of the unsplit one (the last chunk then pays a pass over C for
+  // its powers).  256 x 96, 32 runs of 256 steps, 96 tiles:
+  // 860 -> 432 us, 161 us for the powers after the last of 6 chunks.
+  constexpr int64_t kCUs = 256;
+  auto cost = [&](int64_t per) { return (blocks * ((a.nslots + per - 1) / per) + kCUs - 1) / kCUs * per; };
+  DftArgs b = a;
+  b.per = a.nslots;
+  for (int per = a.nslots - 1; per >= 1; --per)
+    if (4 * cost(per) <= 3 * cost(a.nslots) && cost(per) < cost(b.per)) b.per = per;
+  const int groups = (a.nslots + b.per - 1) / b.per;
+  const bool power = a.last && groups > 1;
+  if (power) b.last = 0;
+  if (groups > 65535) return hipErrorInvalidValue;  // (grid limit)
+  const dim3 grid((unsigned)blocks, (unsigned)groups);
   if (split)
-    hipLaunchKernelGGL(k_dft<true>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL(k_dft<true>, grid, dim3(kThreads), 0, s, b);
   else
-    hipLaunchKernelGGL(k_dft<false>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL(k_dft<false>, grid, dim3(kThreads), 0, s, b);
+  if (power)
+    hipLaunchKernelGGL(k_dft_power, dim3((unsigned)((a.Kp * a.R / 4 + 255) / 256)), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 

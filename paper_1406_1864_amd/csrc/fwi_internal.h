@@ -291,6 +291,7 @@ struct DftArgs {
   int32_t K;
   int64_t model;
   int32_t nslots;       // runs of the launch (slots 0 .. nslots-1)
+  int32_t per;          // runs per workgroup (launch_dft chooses)
   int32_t ntile;        // cell tiles
 };
 // split: bf16 hi/lo operands (three products, FP32 accumulation); else FP32
