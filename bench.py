@@ -541,7 +541,7 @@ def main():
         "config": {"workload": w.name if full else f"{w.name} ({shots} shots, nt {grid.nt_max})",
                    "shots": shots,
                    "grid": [grid.nz, grid.nx], "padded": [Z, X], "nt": int(nt.max()), "receivers_per_shot": nrec_mean,
-                   "misfit": "time_integral", "hmax": HM, "path": "autograd, batched, hipGraph, autotuned",
+                   "misfit": "time_integral", "hmax": HM, "path": "autograd, batched, autotuned",
                    "shots_in_flight": chosen["shots_in_flight"], "tile_rows": chosen["tile_rows"],
                    "graph_steps": chosen["graph_steps"], "prefetch": chosen["prefetch"],
                    "prefetch_reverse": chosen["prefetch_reverse"],
@@ -586,7 +586,7 @@ def main():
         torch.cuda.synchronize()
         pt = time.perf_counter() - t0
         out["plain"] = {"value": ps / pt, "unit": "shot-gradients/s", "shots": ps,
-                        "path": "one shot per launch, one launch per time step, no graph"}
+                        "path": "one shot per launch, one launch per time step"}
         out["speedup_vs_plain"] = value / (ps / pt)
 
     if args.ext >= 0:

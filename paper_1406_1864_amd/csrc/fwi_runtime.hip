@@ -1015,9 +1015,8 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   // FWI_TUNE_LOG set: each candidate's best time goes to stderr
   const bool tune_log = getenv("FWI_TUNE_LOG") != nullptr;
   // ms per time step, best of two timings of `nsteps` launches (two time
-  // steps each for the two-step sweeps, so that they run as the chunk of
-  // graph replays in launch chains they run as in a sweep, not as direct
-  // launches), to keep the choice stable
+  // steps each for the two-step sweeps, in the launch chains that they run in),
+  // to keep the choice stable
   auto timed = [&](Plan& p, int flags, int phase) {
     const bool two = phase == kPhaseRev ? (flags == 0 && p.rev_steps == 2) : p.fwd_steps == 2;
     const int n = two ? 2 * nsteps : nsteps;
@@ -1581,7 +1580,6 @@ ExecChoice dx_choice(const fwi_grid* g, const fwi_exec* ex, int S, bool compact)
   const int Z = g->nz + 2 * g->nsponge;
   const int TZ = (ex && ex->tile_rows > 0) ? ex->tile_rows : default_tile_rows(Z);
   const int pf = (ex && ex->prefetch > 0) ? ex->prefetch : 1;
-  // direct launches: the capture pointer is not baked into any graph
   ExecChoice c{S, TZ, 0, pf, 1, S, TZ, 1, 1};
   c.blk = compact ? 0 : blk_allowed(ex) & 1;
   const int64_t cells = (int64_t)S * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
@@ -1934,8 +1932,7 @@ int fwi_gradient_static(const fwi_grid* grid, const fwi_geometry* geom, const fw
   if (int rc = check_inputs(grid, geom)) return rc;
   if (int rc = check_exec(exec)) return rc;
   if (int rc = check_outputs_hess(hmax, rcv_model, offset_diag, grid)) return rc;
-  // direct launches, heuristic settings: no graph is instantiated and no
-  // candidate is timed
+  // one chain of launches, heuristic settings: no candidate is timed
   fwi_exec ex{};
   if (exec) ex = *exec;
   ex.graph_steps = -1;
