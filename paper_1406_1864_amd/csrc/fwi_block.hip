@@ -222,7 +222,10 @@ struct Patch {
 
 // The patch's cells in the 4-cell ring around the model: cell (i, j) of the
 // ring's sides has index sb + 4 i + j, of its top and bottom rows
-// tb + nx i + j.
+// tb + nx i + j.  One base of each serves a patch because it never holds
+// cells of both sides (patches start a multiple of 4 columns from the model's
+// first one, so those that start left of the model end there) nor of top and
+// bottom (a patch of four rows is not used on models of fewer than three).
 struct Ring {
   int sb, tb;
   uint32_t side, rows;  // bits 4 i + j
@@ -230,8 +233,8 @@ struct Ring {
   __device__ __forceinline__ void find(const P& p, const Dims& d, std::integral_constant<int, PZ>) {
     const int mz0 = p.z - d.N, mx0 = p.xs - d.mx0;
     side = rows = 0;
-    sb = 8 * d.nx + 4 * mz0 + (mx0 < d.nx / 2 ? mx0 + kRadius : 4 * d.nz + mx0 - d.nx);
-    tb = mx0 + d.nx * (mz0 < d.nz / 2 ? mz0 + kRadius : kRadius + mz0 - d.nz);
+    sb = 8 * d.nx + 4 * mz0 + (mx0 < 0 ? mx0 + kRadius : 4 * d.nz + mx0 - d.nx);
+    tb = mx0 + d.nx * (mz0 < 0 ? mz0 + kRadius : kRadius + mz0 - d.nz);
 #pragma unroll
     for (int i = 0; i < PZ; ++i)
 #pragma unroll

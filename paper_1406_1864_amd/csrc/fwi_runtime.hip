@@ -322,8 +322,11 @@ BlkPlan blk_tiling(const Dims& d, int runs, bool rev, bool born, bool chunked) {
   if (!chunked && tiles(6) <= kBlkCUs) return blk_fit(d, kBlkWide, 6, b) ? b : BlkPlan{};
   const int64_t t4 = tiles(4);
   if (t4 <= kBlkCUs && (rev || born)) return blk_fit(d, kBlkWide, 4, b) ? b : BlkPlan{};
-  if (born) return blk_fit(d, kBlkTall, chunked ? 2 : 3, b) ? b : BlkPlan{};
-  if (rev || t4 <= 4 * kBlkCUs) return blk_fit(d, kBlkPair, 4, b) ? b : BlkPlan{};
+  // (a patch of kBlkTall may hold the boundary rings above and below a model
+  // of one or two rows, which have one index base: two rows per thread there)
+  const bool tall = d.nz >= 3;
+  if (born && tall) return blk_fit(d, kBlkTall, chunked ? 2 : 3, b) ? b : BlkPlan{};
+  if (born || rev || t4 <= 4 * kBlkCUs || !tall) return blk_fit(d, kBlkPair, 4, b) ? b : BlkPlan{};
   return blk_fit(d, kBlkTall, chunked ? 2 : 3, b) ? b : BlkPlan{};
 }
 
