@@ -39,6 +39,7 @@
 #include <type_traits>
 
 #include "fwi_internal.h"
+#include "fwi_quotient.h"
 
 namespace fwi {
 namespace {
@@ -271,25 +272,22 @@ __device__ __forceinline__ void sponge_table(Sponge* tab, double sp_a, int N) {
 }
 // The damped cells of one row of a patch take ((1 - g) old + w lap) / (1 + g)
 // (SECOND: (2 c - (1 - g) old + w lap) / (1 + g)) in FP64 instead of the plain
-// update in v.  The division is the product with 1 / (1 + g) and one
-// correction, which rounds like it.  Four cells at a time, so that their
+// update in v.  The division is quotient()'s.  Four cells at a time, so that their
 // table reads and FP64 chains overlap.
 template <bool SECOND>
 __device__ __forceinline__ void damp_row(const Sponge (&t)[4], uint32_t model, const float (&c)[4],
                                          const float (&old)[4], const float (&w)[4], const float (&lap)[4],
                                          float (&v)[4]) {
-  double x[4], q[4];
+  double x[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     x[j] = SECOND ? 2.0 * (double)c[j] - t[j].minus * (double)old[j] + (double)w[j] * (double)lap[j]
                   : t[j].minus * (double)old[j] + (double)w[j] * (double)lap[j];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) q[j] = x[j] * t[j].inv;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) q[j] = fma(fma(-q[j], t[j].plus, x[j]), t[j].inv, q[j]);
+  for (int j = 0; j < 4; ++j) x[j] = quotient(x[j], t[j].plus, t[j].inv);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    float s = (float)q[j];
+    float s = (float)x[j];
     asm volatile("" : "+v"(s));  // computed for every cell: no branch per cell
     v[j] = (model >> j) & 1u ? v[j] : s;
   }
