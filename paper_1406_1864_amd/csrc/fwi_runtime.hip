@@ -290,9 +290,12 @@ bool blk_fit(const Dims& d, int shape, int T, BlkPlan& b) {
   return cut(W, RX, SX, b.nbx, b.sx, 4) && cut(R, RZ, SZ, b.nbz, b.sz, 1);
 }
 
-// Which sweeps run LDS-resident, from the cells of one step (runs * Z * X) and
-// the tiles they make.  Measured per time step against the two-step z sweeps
-// at their best tile rows (us, LDS-resident / z sweep):
+// Which sweeps of `runs` shots in flight run LDS-resident (bit 1: forward, 2:
+// reverse): those whose sponge and receivers the kernels' tables hold, up to a
+// number of cells of one step (runs * Z * X).  Tuned and untuned calls and the
+// plan itself ask here, so that a call gives up two steps per launch only for
+// a sweep that then is LDS-resident.  Measured per time step against the
+// two-step z sweeps at their best tile rows (us, LDS-resident / z sweep):
 //   cells        0.04 M     0.15 M     0.55 M     2.0 M      3.9 M      7.8 M
 //   forward    3.2 / 12.2 3.8 / 13.4 5.0 / 13.9 11.0 / 16.4 15.5 / 19.4 25.4 / 25.2
 //   reverse    3.7 / 12.2 4.3 / 13.1 7.5 / 13.7 20.1 / 18.8 32.5 / 28.9 67.6 / 47.0
@@ -300,13 +303,19 @@ bool blk_fit(const Dims& d, int shape, int T, BlkPlan& b) {
 // fewer bytes and repeat less work at the tiles' margins.
 constexpr int64_t kBlkFwdCells = 8000000, kBlkRevCells = 1600000;
 constexpr int kBlkCUs = 256;
+int blk_takes(const fwi_grid* g, const fwi_geometry* geo, int runs) {
+  if (g->nsponge > kBlkSponge) return 0;
+  for (int s = 0; s < geo->nshot; ++s)
+    if (geo->rec_ptr[s + 1] - geo->rec_ptr[s] > kBlkRecv) return 0;
+  const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
+  return (cells <= kBlkFwdCells ? 1 : 0) | (cells <= kBlkRevCells ? 2 : 0);
+}
 
+// Their tiling, by the tiles they make.
 // chunked: launches end at every 32nd step (windows of captured series or of
 // the extended image), so T divides 32.
 BlkPlan blk_tiling(const Dims& d, int runs, bool rev, bool born, bool chunked) {
   BlkPlan b;
-  if (d.N > kBlkSponge) return b;
-  if ((int64_t)runs * d.Z * d.X > (rev ? kBlkRevCells : kBlkFwdCells)) return b;
   const int W = d.off + d.X - (d.off & ~3), R = d.Z - d.ztop;
   // one tile: the whole record in a few launches
   for (int shape : {kBlkSmall, kBlkWide})
@@ -369,12 +378,10 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   p->llevels = rev2 ? kLamLevels2 : kLamLevels;
   const bool grad = (what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE ||
                      what == FWI_WS_GNHVP);
-  int most_recv = 0;
-  for (int s = 0; s < geo->nshot; ++s) most_recv = std::max(most_recv, geo->rec_ptr[s + 1] - geo->rec_ptr[s]);
-  if (!plain && most_recv <= kBlkRecv) {
+  if (!plain) {
     const bool chunked = what == FWI_WS_EXTIMAGE || ex.graph_steps == 0;  // steps counted in windows of 32
-    if ((ex.blk & 1) && !fwd2) p->bf = blk_tiling(d, p->S, false, what == FWI_WS_BORN || what == FWI_WS_GNHVP, chunked);
-    if ((ex.blk & 2) && grad && !rev2) p->br = blk_tiling(d, p->Sr, true, false, chunked);
+    if ((ex.blk & blk_takes(g, geo, p->S) & 1) && !fwd2) p->bf = blk_tiling(d, p->S, false, what == FWI_WS_BORN || what == FWI_WS_GNHVP, chunked);
+    if ((ex.blk & blk_takes(g, geo, p->Sr) & 2) && grad && !rev2) p->br = blk_tiling(d, p->Sr, true, false, chunked);
     // two sets of levels: neighbouring tiles read each other's inputs
     if (p->bf.T || p->br.T) p->ulevels = std::max(p->ulevels, 2 * kULevels);
     if (p->br.T) p->llevels = kLamLevels2;
@@ -1210,18 +1217,15 @@ void untuned_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* 
   if (!autos || geo->nshot == 0) return;
   const int runs = std::max(1, std::min(c.S, geo->nshot));
   const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
-  int most_recv = 0;
-  for (int s = 0; s < geo->nshot; ++s) most_recv = std::max(most_recv, geo->rec_ptr[s + 1] - geo->rec_ptr[s]);
-  const bool blk = g->nsponge <= kBlkSponge && most_recv <= kBlkRecv;
-  if ((autos & 1) && !(blk && cells <= kBlkFwdCells)) {
+  const int rest = autos & ~blk_takes(g, geo, runs);  // sweeps that stay z sweeps
+  if (rest & 1) {
     const bool two = !g->free_surface && what != FWI_WS_BORN && what != FWI_WS_GNHVP;
     c.fsteps = two ? 2 : 1;
     c.pf_fwd = 1;
     if (!c.TZr) c.TZr = c.TZ;
     c.TZ = two && cells >= 12000000 ? 32 : 16;
   }
-  if ((autos & 2) && what != FWI_WS_FORWARD && what != FWI_WS_HESSIAN && what != FWI_WS_BORN &&
-      !(blk && cells <= kBlkRevCells)) {
+  if ((rest & 2) && what != FWI_WS_FORWARD && what != FWI_WS_HESSIAN && what != FWI_WS_BORN) {
     c.rsteps = g->free_surface ? 1 : 2;
     c.TZr = cells < 5000000 ? 8 : cells < 12000000 || g->free_surface ? 16 : cells < 24000000 ? 32 : 64;
   }
@@ -1419,12 +1423,10 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
       // the tuned shots in flight are the z sweeps': whether the LDS-resident
       // ones take over is decided for every shot at once, which suits them best
       const int runs = std::min(std::max(geo->nshot, 1), 64);
-      const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
-      if (cells > kBlkFwdCells) c.blk &= ~1;
-      if (cells > kBlkRevCells) c.blk &= ~2;
+      c.blk &= blk_takes(g, geo, runs);
       if (c.blk & 1) c.fsteps = 1;
       if (c.blk & 2) c.rsteps = 1;
-      if (c.blk == 3 || (c.blk && forward_only)) {
+      if (c.blk == 3 || ((c.blk & 1) && forward_only)) {
         c.S = runs;
         c.Sr = 0;
       }
@@ -1579,14 +1581,15 @@ DxGeo dx_side(const fwi_geometry* geo, const DxGroup& gr, bool receivers) {
   return o;
 }
 
-ExecChoice dx_choice(const fwi_grid* g, const fwi_exec* ex, int S, bool compact) {
+// side: the runs' geometry (dx_side)
+ExecChoice dx_choice(const fwi_grid* g, const fwi_geometry* side, const fwi_exec* ex, int S, bool compact) {
   const int Z = g->nz + 2 * g->nsponge;
   const int TZ = (ex && ex->tile_rows > 0) ? ex->tile_rows : default_tile_rows(Z);
   const int pf = (ex && ex->prefetch > 0) ? ex->prefetch : 1;
   ExecChoice c{S, TZ, 0, pf, 1, S, TZ, 1, 1};
   c.blk = compact ? 0 : blk_allowed(ex) & 1;
   const int64_t cells = (int64_t)S * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
-  if (c.blk && (cells > kBlkFwdCells || g->nsponge > kBlkSponge)) {
+  if (c.blk && !(blk_takes(g, side, S) & 1)) {
     c.fsteps = 2;  // two steps per launch, rows as in untuned_choice()
     c.TZ = cells < 12000000 ? 16 : 32;
   }
@@ -1618,7 +1621,7 @@ int dx_layout(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, in
       DxGeo dg = dx_side(geo, gr, side == 0);
       const int S = std::min(Sreq, std::max(dg.g.nshot, 1));
       Smax = std::max(Smax, S);
-      auto p = build_plan(g, &dg.g, dx_choice(g, ex, S, compact), 0, FWI_WS_FORWARD, 0);
+      auto p = build_plan(g, &dg.g, dx_choice(g, &dg.g, ex, S, compact), 0, FWI_WS_FORWARD, 0);
       o.plan = std::max(o.plan, (size_t)p->L.total);
     }
   }
@@ -2076,7 +2079,7 @@ int fwi_offset_diag_exact(const fwi_grid* grid, const fwi_geometry* geom, const 
       const bool rcv = side == 0;
       DxGeo dg = dx_side(geom, gr, rcv);
       const int S = std::min(Sreq, std::max(dg.g.nshot, 1));
-      auto p = build_plan(grid, &dg.g, dx_choice(grid, exec, S, compact), 0, FWI_WS_FORWARD, 0);
+      auto p = build_plan(grid, &dg.g, dx_choice(grid, &dg.g, exec, S, compact), 0, FWI_WS_FORWARD, 0);
       if (p->L.total > o.plan || p->S > o.S) return fail(FWI_ERR_STATE, "exact offset diagonal: plan outgrew its region");
       if ((rc = begin_call(*p, workspace, v, s))) return rc;
       err = &at<Header>(workspace, p->L.hdr)->err;

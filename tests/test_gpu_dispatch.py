@@ -1,0 +1,39 @@
+"""Autotuned calls on both sides of what the LDS-resident sweeps hold (1024
+receivers of a shot, 128 sponge cells) against named z sweeps.
+
+Every form has the same operations in the same order.  Two reverse steps per
+launch, named or tuned, come with an even snapshot spacing: the named call
+takes the tuned one's reverse steps, and all results have the same bits.
+"""
+import numpy as np
+import pytest
+
+from paper_1406_1864_amd import binding as B
+from paper_1406_1864_amd.synthetic import Geometry, Grid, gaussian_anomaly, random_traces, ricker
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("N,nrec", [(20, 60), (20, 1025), (129, 60)])
+def test_tuned_calls_have_the_named_sweeps_bits(N, nrec):
+    nx, nz, ns, nt = 200, 90, 3, 118
+    grid = Grid(nz, nx, 10.0, 1e-3, nt, N, 2300.0)
+    v = gaussian_anomaly(nz, nx, 2000.0, 0.12, 15.0)
+    iz, ix = np.divmod(np.arange(nrec, dtype=np.int32), nx)
+    geom = Geometry(np.full(ns, 4, np.int32), np.array([5, 100, 190], np.int32),
+                    np.arange(ns + 1, dtype=np.int32) * nrec, np.tile(iz, ns), np.tile(ix, ns),
+                    np.array([nt, nt - 7, nt - 40], np.int32))
+    wav = ricker(14.0, 1e-3, nt).astype(np.float32)
+    d = random_traces(geom, nt, seed=5, scale=1e-2)
+
+    def calls(ex):
+        return [B.forward(v, wav, grid, geom, ex), B.hessian_diag(v, wav, grid, geom, B.HESS_EQ1, exec_=ex),
+                *B.gradient(v, wav, grid, geom, d, "int", ex, hmax=2)]
+    tuned = B.make_exec(autotune=1)
+    a = calls(tuned)
+    steps = B.fwi_exec_query(grid, geom, tuned, B.WS_GRADIENT)["reverse_steps"]
+    b = calls(B.make_exec(tile_rows=16, reverse_steps=steps, graph_steps=-1))
+    for k, (x, y) in enumerate(zip(a, b)):
+        assert bool(torch.isfinite(x).all()) and float(x.abs().max()) > 0, k
+        assert torch.equal(x, y), k
