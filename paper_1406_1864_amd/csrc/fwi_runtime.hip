@@ -1231,7 +1231,23 @@ void untuned_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* 
   }
 }
 
-std::vector<uint64_t> tune_key(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what) {
+bool forward_only(int what) { return what == FWI_WS_FORWARD || what == FWI_WS_HESSIAN || what == FWI_WS_BORN; }
+
+// Shots in flight that a tuned call is sized for and that the LDS-resident
+// sweeps take.
+int tuned_runs(const fwi_geometry* geo) { return std::min(std::max(geo->nshot, 1), 64); }
+
+// The sweeps of an autotuned call that run LDS-resident (bits of blk_takes).
+// The tuned shots in flight are the z sweeps': whether the LDS-resident ones
+// take over is decided for every shot at once, which suits them best.
+int tuned_blk(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex) {
+  return ex->shots_in_flight > 0 ? 0 : blk_allowed(ex) & blk_takes(g, geo, tuned_runs(geo));
+}
+// whether that is every sweep of the call: nothing is left to time
+bool nothing_to_tune(int blk, int what) { return blk == 3 || ((blk & 1) && forward_only(what)); }
+
+// untimed: the key of a call with nothing to tune
+std::vector<uint64_t> tune_key(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, bool untimed) {
   Hasher h;
   h.grid(*g);
   h.pod(geo->nshot);
@@ -1263,6 +1279,9 @@ std::vector<uint64_t> tune_key(const fwi_grid* g, const fwi_geometry* geo, const
     a.pod(prop.multiProcessorCount);
     k.push_back(a.h);
   }
+  // (in a workspace too small for the LDS-resident sweeps the same call is
+  // timed: its settings are another entry)
+  if (untimed) k.push_back(1);
   return k;
 }
 
@@ -1373,61 +1392,43 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   if (int rc = check_exec(ex)) return rc;
   ExecChoice c = base_choice(g, geo, ex);
   const int branches = c.branches, blk = c.blk;  // not tuned: the tuner times with the former, without the latter
-  const bool tune = !plain && ex && ex->autotune && !sizing_only;
+  const bool tuned_call = !plain && ex && ex->autotune;
   const uint64_t ikey = inputs_hash(g, geo);
   std::lock_guard<std::mutex> lock(g_mutex);
-  if (!plain && ex && ex->autotune) {
+  if (tuned_call) {
     // the workspace is sized for the largest candidate
-    if (!(ex->shots_in_flight > 0)) c.S = std::min(std::max(geo->nshot, 1), 64);
+    if (!(ex->shots_in_flight > 0)) c.S = tuned_runs(geo);
     if (!(ex->tile_rows > 0)) c.TZ = 32;
     c.Sr = 0;  // reverse buffers sized for the forward's maximum
     if (!(ex->reverse_steps > 0)) c.rsteps = 2;  // and for the two-step sweeps' levels
     if (!(ex->forward_steps > 0)) c.fsteps = 2;
   }
-  if (tune) {
-    const auto tk = tune_key(g, geo, ex, what);
-    auto it = g_tuned.find(tk);
-    ExecChoice t = c;
-    if (it != g_tuned.end()) {
-      c = it->second;
-    } else if (cache_lookup(tk, t) && t.S <= c.S && t.Sr <= c.S) {
-      g_tuned[tk] = t;
-      c = t;
-    } else {
-      t = c;
-      int rc = autotune(g, geo, ex, what, ikey, ws, ws_bytes, v, wavelet, wstride, s, t);
-      if (rc) return rc;
-      g_tuned[tk] = t;
-      cache_store(tk, t);
-      c = t;
-    }
-  }
-  c.branches = branches;
-  // Two steps per launch by request or tuning come with an even snapshot
-  // spacing, whatever form then runs the sweep: the reconstruction's rounding
-  // (1e-5 of the gradient over 4000 steps) depends on where it restarts.
-  // Tuned calls are sized for the spacing that keeps more.
-  c.even_k = c.rsteps == 2 && !plain && !g->free_surface && !(sizing_only && !compact && ex && ex->autotune);
-  const ExecChoice tuned = c;
-  const bool forward_only = what == FWI_WS_FORWARD || what == FWI_WS_HESSIAN || what == FWI_WS_BORN;
+  const int resident = tuned_call ? tuned_blk(g, geo, ex) : 0;
+  ExecChoice tuned;
   // compact: what a workspace of the one-step z sweeps' (tuned calls: the z
   // sweeps') size holds
   auto settle = [&](bool small) {
     c = tuned;
+    // Two steps per launch by request or tuning come with an even snapshot
+    // spacing: the reconstruction's rounding (1e-5 of the gradient over 4000
+    // steps) depends on where it restarts.  Tuned calls are sized for the
+    // spacing that keeps more.
+    c.even_k = c.rsteps == 2 && !plain && !g->free_surface && !(sizing_only && !compact && tuned_call);
     c.blk = small ? 0 : blk;
-    if (small && forward_only) c.fsteps = 1;
+    if (small && forward_only(what)) c.fsteps = 1;
     if (plain || small) return;
-    if (!(ex && ex->autotune)) {
+    if (!tuned_call) {
       untuned_choice(g, geo, ex, what, c);
-    } else if (c.blk && !(ex->shots_in_flight > 0)) {
-      // the tuned shots in flight are the z sweeps': whether the LDS-resident
-      // ones take over is decided for every shot at once, which suits them best
-      const int runs = std::min(std::max(geo->nshot, 1), 64);
-      c.blk &= blk_takes(g, geo, runs);
-      if (c.blk & 1) c.fsteps = 1;
-      if (c.blk & 2) c.rsteps = 1;
-      if (c.blk == 3 || ((c.blk & 1) && forward_only)) {
-        c.S = runs;
+    } else if (!(ex->shots_in_flight > 0)) {
+      c.blk = resident;
+      if (resident & 1) c.fsteps = 1;
+      if (resident & 2) {
+        // the spacing is the untuned call's
+        c.rsteps = 1;
+        c.even_k = 0;
+      }
+      if (nothing_to_tune(resident, what)) {
+        c.S = tuned_runs(geo);
         c.Sr = 0;
       }
     }
@@ -1448,6 +1449,44 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
       while (g_plans.size() > 16) g_plans.pop_back();
     }
   };
+  // the settings of the call's key: this process', the file's or new ones
+  auto look_up = [&](bool untimed) -> int {
+    const auto tk = tune_key(g, geo, ex, what, untimed);
+    auto it = g_tuned.find(tk);
+    ExecChoice t = tuned;
+    if (it != g_tuned.end()) {
+      t = it->second;
+    } else {
+      if (!(cache_lookup(tk, t) && t.S <= tuned.S && t.Sr <= tuned.S)) {
+        t = tuned;
+        if (untimed) {
+          t = c;
+          t.Sr = t.S;
+          t.TZr = t.TZ;
+        } else if (int rc = autotune(g, geo, ex, what, ikey, ws, ws_bytes, v, wavelet, wstride, s, t)) {
+          return rc;
+        }
+        cache_store(tk, t);
+      }
+      g_tuned[tk] = t;
+    }
+    if (!untimed) {
+      tuned = t;
+      tuned.branches = branches;
+    }
+    return FWI_OK;
+  };
+  tuned = c;
+  if (tuned_call && !sizing_only) {
+    if (nothing_to_tune(resident, what)) {
+      // 150 to 290 ms of candidates in a first call that takes 2 to 3 ms (3
+      // shots of 200 x 90 cells, 16 of 256 x 96) had no part in what ran
+      settle(false);
+      find_or_build();
+      if (out->L.total <= ws_bytes) return look_up(true);
+    }
+    if (int rc = look_up(false)) return rc;
+  }
   settle(compact);
   find_or_build();
   if (!sizing_only && out->L.total > ws_bytes) {
@@ -1703,7 +1742,8 @@ int fwi_exec_query(const fwi_grid* grid, const fwi_geometry* geom, const fwi_exe
   if (!plain && !(exec && exec->autotune)) untuned_choice(grid, geom, exec, what, c);
   if (!plain && exec && exec->autotune) {
     std::lock_guard<std::mutex> lock(g_mutex);
-    const std::vector<uint64_t> tk = tune_key(grid, geom, exec, what);
+    const std::vector<uint64_t> tk =
+        tune_key(grid, geom, exec, what, nothing_to_tune(tuned_blk(grid, geom, exec), what));
     auto it = g_tuned.find(tk);
     ExecChoice t{};
     if (it != g_tuned.end()) {

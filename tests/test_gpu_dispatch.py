@@ -37,3 +37,36 @@ def test_tuned_calls_have_the_named_sweeps_bits(N, nrec):
     for k, (x, y) in enumerate(zip(a, b)):
         assert bool(torch.isfinite(x).all()) and float(x.abs().max()) > 0, k
         assert torch.equal(x, y), k
+
+
+def test_lds_resident_calls_are_not_timed(capfd, monkeypatch):
+    """Where every sweep of a tuned call runs LDS-resident no candidate is
+    timed and the results have the untuned call's bits, snapshot spacing
+    included; in a workspace of the z sweeps' size the same call is timed."""
+    monkeypatch.setenv("FWI_TUNE_LOG", "1")
+    nx, nz, ns, nt = 90, 50, 2, 119    # 11 steps between the snapshots of the first shot, 12 at an even spacing
+    grid = Grid(nz, nx, 10.0, 1e-3, nt, 10, 2300.0)
+    v = gaussian_anomaly(nz, nx, 2000.0, 0.12, 9.0)
+    ix = np.arange(0, nx, 5, dtype=np.int32)
+    geom = Geometry(np.full(ns, 3, np.int32), np.array([5, 80], np.int32), np.arange(ns + 1, dtype=np.int32) * len(ix),
+                    np.full(ns * len(ix), 1, np.int32), np.tile(ix, ns), np.array([nt, nt - 19], np.int32))
+    wav = ricker(14.0, 1e-3, nt).astype(np.float32)
+    d = random_traces(geom, nt, seed=5, scale=1e-2)
+    tuned = B.make_exec(autotune=1)
+
+    def timed(call):
+        out = call()
+        torch.cuda.synchronize()
+        return out, capfd.readouterr().err.count("[fwi tune]")
+
+    a, n = timed(lambda: B.gradient(v, wav, grid, geom, d, "int", tuned))
+    assert n == 0
+    b, n = timed(lambda: B.gradient(v, wav, grid, geom, d, "int", None))
+    assert n == 0 and all(torch.equal(x, y) for x, y in zip(a[:3], b[:3]))
+    ref, n = timed(lambda: B.forward(v, wav, grid, geom, tuned))
+    assert n == 0
+    size = B.fwi_workspace_bytes(grid, geom, B.make_exec(tile_rows=32), B.WS_FORWARD)
+    assert size < B.fwi_workspace_bytes(grid, geom, tuned, B.WS_FORWARD)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    got, n = timed(lambda: B.forward(v, wav, grid, geom, tuned, ws=ws))
+    assert n > 0 and torch.equal(got, ref)
