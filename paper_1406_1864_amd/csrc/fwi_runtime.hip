@@ -14,6 +14,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstdio>
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <list>
@@ -191,7 +192,8 @@ struct ExecChoice {
   int S, TZ, graph_steps, pf_fwd, pf_rev, Sr, TZr, rsteps, fsteps;
   int branches = 0;  // independent launch chains of the two-step sweeps (0: kDefaultBranches)
   int even_k = 0;    // snapshot spacing rounded up to even
-  int blk = 0;       // LDS-resident sweeps where blk_tiling() has one: 1 forward, 2 reverse
+  int blk = 0;       // LDS-resident sweeps where blk_takes() has them: 1 forward, 2 reverse
+  int act = 1;       // an arrival map where one pays
 };
 
 std::mutex g_mutex;
@@ -392,7 +394,7 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   // load (0.5 us of a launch's 10).
   p->act_nx = (d.P + kActCols - 1) / kActCols;
   p->act_nz = (d.Z + kActRows - 1) / kActRows;
-  p->act_f = fwd2 || (p->bf.T && (int64_t)p->bf.nbx * p->bf.nbz * p->S > kBlkCUs);
+  p->act_f = ex.act && (fwd2 || (p->bf.T && (int64_t)p->bf.nbx * p->bf.nbz * p->S > kBlkCUs));
   p->XT2 = kWavesPerBlock * ((d.X + kBlk2 - 1) / kBlk2);
   const double eta_max = 3.0 * g->v_ref * std::log(1e3) / (2.0 * d.N * g->dx);
   p->sp_a = 0.5 * g->dt * eta_max / ((double)d.N * d.N);
@@ -400,8 +402,10 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   const int ns = geo->nshot;
   p->ntrace = ns > 0 ? geo->rec_ptr[ns] : 0;
   p->trace_shot.assign(std::max(p->ntrace, 1), 0);
-  p->rcell.assign(std::max(p->ntrace, 1), make_int2(0, 0));
-  for (int r = 0; r < p->ntrace; ++r) p->rcell[r] = make_int2(geo->rec_iz[r] + d.N, geo->rec_ix[r] + d.mx0);
+  if (p->bf.T || p->br.T) {
+    p->rcell.assign(std::max(p->ntrace, 1), make_int2(0, 0));
+    for (int r = 0; r < p->ntrace; ++r) p->rcell[r] = make_int2(geo->rec_iz[r] + d.N, geo->rec_ix[r] + d.mx0);
+  }
   p->shots.resize(std::max(ns, 1));
   int max_nsnap = 0;
   for (int s = 0; s < ns; ++s) {
@@ -553,8 +557,10 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   L.rrows2 = take(sizeof(RmapRow) * p->rrows2.size());
   L.rmaps2 = take(sizeof(int32_t) * p->rmaps2.size());
   L.trace_shot = take(sizeof(int32_t) * p->trace_shot.size());
-  L.rcell = take(sizeof(int2) * p->rcell.size());
-  L.act = take(p->act_f ? sizeof(int32_t) * (size_t)p->act_nx * p->act_nz * p->ncs : 0);
+  // (nothing for plans without them: a workspace of the z sweeps' size holds
+  // what it held before there were other forms)
+  L.rcell = p->rcell.empty() ? o : take(sizeof(int2) * p->rcell.size());
+  L.act = p->act_f ? take(sizeof(int32_t) * (size_t)p->act_nx * p->act_nz * p->ncs) : o;
   L.w = take(sizeof(float) * d.field);
   L.traces = take(sizeof(float) * (size_t)g->nt_max * std::max(p->ntrace, 1));
   L.jpart = take(sizeof(double) * std::max(p->ntrace, 1));
@@ -852,8 +858,9 @@ int upload_tables(const Plan& p, void* ws, hipStream_t s) {
                          hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(at<char>(ws, p.L.rmaps2), p.rmaps2.data(), sizeof(int32_t) * p.rmaps2.size(),
                          hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(at<char>(ws, p.L.rcell), p.rcell.data(), sizeof(int2) * p.rcell.size(),
-                         hipMemcpyHostToDevice, s));
+  if (!p.rcell.empty())
+    HIP_TRY(hipMemcpyAsync(at<char>(ws, p.L.rcell), p.rcell.data(), sizeof(int2) * p.rcell.size(),
+                           hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(at<char>(ws, p.L.trace_shot), p.trace_shot.data(),
                          sizeof(int32_t) * p.trace_shot.size(), hipMemcpyHostToDevice, s));
   return FWI_OK;
@@ -1374,15 +1381,18 @@ uint64_t plan_key(uint64_t ikey, int what, int plain, const ExecChoice& c, int e
   h.pod(c.branches);
   h.pod(c.even_k);
   h.pod(c.blk);
+  h.pod(c.act);
   h.pod(ext_h);
   return h.h;
 }
 
+int ws_short(size_t ws_bytes, size_t need) {
+  return fail(FWI_ERR_WORKSPACE,
+              "workspace of " + std::to_string(ws_bytes) + " bytes, need " + std::to_string(need));
+}
+
 int ws_check(const Plan& p, size_t ws_bytes) {
-  if (ws_bytes < p.L.total)
-    return fail(FWI_ERR_WORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, need " +
-                                       std::to_string(p.L.total));
-  return FWI_OK;
+  return ws_bytes < p.L.total ? ws_short(ws_bytes, p.L.total) : FWI_OK;
 }
 
 int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, void* ws,
@@ -1415,6 +1425,7 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
     // spacing that keeps more.
     c.even_k = c.rsteps == 2 && !plain && !g->free_surface && !(sizing_only && !compact && tuned_call);
     c.blk = small ? 0 : blk;
+    c.act = small ? 0 : 1;
     if (small && forward_only(what)) c.fsteps = 1;
     if (plain || small) return;
     if (!tuned_call) {
@@ -1497,15 +1508,18 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
 }
 
 // Whether a workspace holds the call: at the size fwi_workspace_bytes reports,
-// or at that of the z sweeps (get_plan then runs those).
+// or at that of the z sweeps without an arrival map, which is what the call
+// needed before there were other forms (get_plan then runs those).
 int size_check(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, size_t ws_bytes,
                int ext_h = -1) {
-  std::shared_ptr<Plan> p;
+  size_t need = SIZE_MAX;
   for (bool compact : {false, true}) {
+    std::shared_ptr<Plan> p;
     if (int rc = get_plan(g, geo, ex, what, nullptr, 0, nullptr, nullptr, 0, nullptr, p, true, ext_h, compact)) return rc;
-    if (ws_bytes >= p->L.total) return FWI_OK;
+    need = std::min(need, p->L.total);
+    if (ws_bytes >= need) return FWI_OK;
   }
-  return ws_check(*p, ws_bytes);
+  return ws_short(ws_bytes, need);
 }
 
 int common_checks(const fwi_grid* g, const fwi_geometry* geo, const float* v, const float* wavelet,
@@ -1627,6 +1641,7 @@ ExecChoice dx_choice(const fwi_grid* g, const fwi_geometry* side, const fwi_exec
   const int pf = (ex && ex->prefetch > 0) ? ex->prefetch : 1;
   ExecChoice c{S, TZ, 0, pf, 1, S, TZ, 1, 1};
   c.blk = compact ? 0 : blk_allowed(ex) & 1;
+  c.act = compact ? 0 : 1;
   const int64_t cells = (int64_t)S * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
   if (c.blk && !(blk_takes(g, side, S) & 1)) {
     c.fsteps = 2;  // two steps per launch, rows as in untuned_choice()

@@ -1,4 +1,6 @@
 """Host checks of the rules that choose a call's sweeps (no GPU needed)."""
+import re
+
 import numpy as np
 import pytest
 
@@ -24,3 +26,44 @@ def test_tuned_calls_keep_two_steps_past_the_lds_tables(N, nrec):
         tuned = B.fwi_workspace_bytes(grid, geom, B.make_exec(autotune=1), what)
         untuned = B.fwi_workspace_bytes(grid, geom, None, what)
         assert tuned >= untuned, what
+
+
+# Sizes that the library reported for these calls, and accepted, while it had
+# only the z sweeps and no arrival map: 3 shots of 130 x 90 cells, sponge 11,
+# 100 receivers, 110 samples.
+Z_SIZES = {
+    "none": dict(forward=1466880, hessian=1607424, gradient=7401216, autograd=7401216, image=17650432, born=2793984,
+                 gn=8728320),
+    "two": dict(forward=1466880, hessian=1607424, gradient=9368576, autograd=9368576, image=28603392, born=2793984,
+                gn=10302464),
+    "tuned": dict(forward=1466880, hessian=1607424, gradient=9368576, autograd=9368576, image=28603392, born=2793984,
+                  gn=10302464),
+}
+EXEC = {"none": {}, "two": dict(forward_steps=2, reverse_steps=2), "tuned": dict(autotune=1)}
+
+
+def needed(call):
+    """The bytes that a call refused for its workspace says it needs: the
+    least it accepts (raised before any HIP call)."""
+    with pytest.raises(B.FwiError) as e:
+        call()
+    assert e.value.code == B.FWI_ERR_WORKSPACE
+    return int(re.search(r"need (\d+)", str(e.value)).group(1))
+
+
+@pytest.mark.parametrize("ex", sorted(EXEC))
+def test_workspaces_of_the_z_sweeps_sizes_are_accepted(ex):
+    grid, geom = problem(130, 90, 11, 3, 100, nt=110)
+    p = 0x1000
+    a = (grid, geom, B.make_exec(**EXEC[ex]), p, p, 0)
+    calls = {
+        "forward": lambda: B.fwi_forward(*a, p, p, 16, stream=0),
+        "hessian": lambda: B.fwi_hessian_diag(*a, B.HESS_EQ1, 0, "pm", p, p, 16, stream=0),
+        "gradient": lambda: B.fwi_gradient(*a, p, "int", p, p, None, 0, "pm", None, p, 16, stream=0),
+        "autograd": lambda: B.fwi_misfit_forward(*a, p, "int", p, p, 16, stream=0),
+        "image": lambda: B.fwi_extended_image(*a, p, "int", p, None, 4, p, p, 16, stream=0),
+        "born": lambda: B.fwi_born(*a, p, p, p, 16, stream=0),
+        "gn": lambda: B.fwi_gn_hvp(*a, p, "int", p, p, p, 16, stream=0),
+    }
+    for name, call in calls.items():
+        assert needed(call) <= Z_SIZES[ex][name], name

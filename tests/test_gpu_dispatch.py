@@ -5,6 +5,8 @@ Every form has the same operations in the same order.  Two reverse steps per
 launch, named or tuned, come with an even snapshot spacing: the named call
 takes the tuned one's reverse steps, and all results have the same bits.
 """
+import re
+
 import numpy as np
 import pytest
 
@@ -70,3 +72,26 @@ def test_lds_resident_calls_are_not_timed(capfd, monkeypatch):
     ws = torch.empty(size, dtype=torch.uint8, device="cuda")
     got, n = timed(lambda: B.forward(v, wav, grid, geom, tuned, ws=ws))
     assert n > 0 and torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("ex", [{}, dict(forward_steps=2, reverse_steps=2)])
+def test_the_least_workspace_gives_the_same_bits(ex):
+    """The z sweeps without an arrival map, in exactly the bytes that a
+    refused call asks for."""
+    nx, nz, N, nt = 290, 60, 15, 90
+    grid = Grid(nz, nx, 10.0, 1e-3, nt, N, 2300.0)
+    v = gaussian_anomaly(nz, nx, 2000.0, 0.12, 15.0)
+    ix = np.arange(0, nx, 4, dtype=np.int32)
+    geom = Geometry(np.array([3, 40], np.int32), np.array([7, 250], np.int32), np.arange(3, dtype=np.int32) * len(ix),
+                    np.full(2 * len(ix), 2, np.int32), np.tile(ix, 2), np.array([nt, nt - 9], np.int32))
+    wav = ricker(14.0, 1e-3, nt).astype(np.float32)
+    d = random_traces(geom, nt, seed=5, scale=1e-2)
+    ex = B.make_exec(**ex)
+    for what, call in ((B.WS_GRADIENT, lambda ws: B.gradient(v, wav, grid, geom, d, "int", ex, hmax=2, ws=ws)),
+                       (B.WS_EXTIMAGE, lambda ws: B.extended_image(v, wav, grid, geom, d, 2, "int", ex, ws=ws))):
+        with pytest.raises(B.FwiError) as e:
+            call(torch.empty(16, dtype=torch.uint8, device="cuda"))
+        need = int(re.search(r"need (\d+)", str(e.value)).group(1))
+        assert need < B.fwi_workspace_bytes(grid, geom, ex, what, 2)
+        small, full = call(torch.empty(need, dtype=torch.uint8, device="cuda")), call(None)
+        assert all(torch.equal(x, y) for x, y in zip(small, full))
