@@ -192,6 +192,7 @@ struct ExecChoice {
   int S, TZ, graph_steps, pf_fwd, pf_rev, Sr, TZr, rsteps, fsteps;
   int branches = 0;  // independent launch chains of the two-step sweeps (0: kDefaultBranches)
   int even_k = 0;    // snapshot spacing rounded up to even
+  int win2 = 0;      // the extended image's windows count launches, also those of two steps
   int blk = 0;       // LDS-resident sweeps where blk_takes() has them: 1 forward, 2 reverse
   int act = 1;       // an arrival map where one pays
 };
@@ -402,7 +403,8 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   const int ns = geo->nshot;
   p->ntrace = ns > 0 ? geo->rec_ptr[ns] : 0;
   p->trace_shot.assign(std::max(p->ntrace, 1), 0);
-  if (p->bf.T || p->br.T) {
+  // (also where tuning may yet choose such a sweep: the size it is given)
+  if (!plain && ((ex.blk & blk_takes(g, geo, p->S) & 1) || (grad && (ex.blk & blk_takes(g, geo, p->Sr) & 2)))) {
     p->rcell.assign(std::max(p->ntrace, 1), make_int2(0, 0));
     for (int r = 0; r < p->ntrace; ++r) p->rcell[r] = make_int2(geo->rec_iz[r] + d.N, geo->rec_ix[r] + d.mx0);
   }
@@ -535,10 +537,11 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   p->born = (what == FWI_WS_BORN || what == FWI_WS_GNHVP) ? 1 : 0;
   const bool ext = (what == FWI_WS_EXTIMAGE && ext_h >= 0);
   p->ext_h = ext ? ext_h : -1;
-  // the ring holds the reverse steps of graph_steps launches (untuned calls:
-  // graph_steps steps, whatever form runs the sweep)
+  // the ring holds the reverse steps of graph_steps launches (calls that
+  // neither name nor tune the steps: graph_steps steps, whatever form runs
+  // the sweep)
   const int win = p->graph_steps > 0 && !p->br.T ? p->graph_steps : 32;
-  p->ext_T = !ext ? 0 : ex.even_k ? win * p->rev_steps : (win + p->rev_steps - 1) / p->rev_steps * p->rev_steps;
+  p->ext_T = !ext ? 0 : ex.win2 ? win * p->rev_steps : (win + p->rev_steps - 1) / p->rev_steps * p->rev_steps;
   Layout& L = p->L;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -1061,7 +1064,7 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
       // sweep has twice the wavefield levels)
       auto prepare = [&](int fs) -> std::shared_ptr<Plan> {
         ExecChoice c{S, TZ, best.graph_steps, PFs[0], RFs[0], S, TZ, rs_max, fs, best.branches};
-        c.even_k = rs_max == 2;
+        c.even_k = c.win2 = rs_max == 2;
         auto p = build_plan(g, geo, c, 0, what, 0);
         if (p->L.total > ws_bytes) return nullptr;
         p->act_f = false;  // the first steps reach few tiles: time whole launches
@@ -1380,6 +1383,7 @@ uint64_t plan_key(uint64_t ikey, int what, int plain, const ExecChoice& c, int e
   h.pod(c.fsteps);
   h.pod(c.branches);
   h.pod(c.even_k);
+  h.pod(c.win2);
   h.pod(c.blk);
   h.pod(c.act);
   h.pod(ext_h);
@@ -1422,8 +1426,9 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
     // Two steps per launch by request or tuning come with an even snapshot
     // spacing: the reconstruction's rounding (1e-5 of the gradient over 4000
     // steps) depends on where it restarts.  Tuned calls are sized for the
-    // spacing that keeps more.
-    c.even_k = c.rsteps == 2 && !plain && !g->free_surface && !(sizing_only && !compact && tuned_call);
+    // spacing that keeps more and the longer windows.
+    c.win2 = c.rsteps == 2 && !plain && !g->free_surface;
+    c.even_k = c.win2 && !(sizing_only && !compact && tuned_call);
     c.blk = small ? 0 : blk;
     c.act = small ? 0 : 1;
     if (small && forward_only(what)) c.fsteps = 1;
@@ -1436,7 +1441,7 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
       if (resident & 2) {
         // the spacing is the untuned call's
         c.rsteps = 1;
-        c.even_k = 0;
+        c.even_k = c.win2 = 0;
       }
       if (nothing_to_tune(resident, what)) {
         c.S = tuned_runs(geo);

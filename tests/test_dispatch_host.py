@@ -67,3 +67,11 @@ def test_workspaces_of_the_z_sweeps_sizes_are_accepted(ex):
     }
     for name, call in calls.items():
         assert needed(call) <= Z_SIZES[ex][name], name
+
+
+def test_tuned_image_is_sized_for_two_steps_per_launch():
+    """Tuned extended images of over 1.6 M cells a step run the two-step reverse
+    sweep, whose windows hold twice the steps."""
+    grid, geom = problem(1000, 400, 20, 4, 50)
+    two = B.fwi_workspace_bytes(grid, geom, B.make_exec(forward_steps=2, reverse_steps=2), B.WS_EXTIMAGE, 3)
+    assert B.fwi_workspace_bytes(grid, geom, B.make_exec(autotune=1), B.WS_EXTIMAGE, 3) >= two

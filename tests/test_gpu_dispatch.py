@@ -95,3 +95,23 @@ def test_the_least_workspace_gives_the_same_bits(ex):
         assert need < B.fwi_workspace_bytes(grid, geom, ex, what, 2)
         small, full = call(torch.empty(need, dtype=torch.uint8, device="cuda")), call(None)
         assert all(torch.equal(x, y) for x, y in zip(small, full))
+
+
+def test_tuned_image_past_the_lds_resident_sizes():
+    """An autotuned extended image of 1.8 M cells a step in the workspace that
+    is reported for it, against the named call of the tuned steps."""
+    nx, nz, ns, nt = 1000, 400, 4, 70
+    grid = Grid(nz, nx, 10.0, 1e-3, nt, 20, 2300.0)
+    v = gaussian_anomaly(nz, nx, 2000.0, 0.12, 15.0)
+    ix = np.arange(0, nx, 10, dtype=np.int32)
+    geom = Geometry(np.full(ns, 4, np.int32), np.array([100, 300, 600, 900], np.int32),
+                    np.arange(ns + 1, dtype=np.int32) * len(ix), np.full(ns * len(ix), 2, np.int32), np.tile(ix, ns),
+                    np.full(ns, nt, np.int32))
+    wav = ricker(20.0, 1e-3, nt).astype(np.float32)
+    d = random_traces(geom, nt, seed=5, scale=1e-2)
+    tuned = B.make_exec(autotune=1)
+    a = B.extended_image(v, wav, grid, geom, d, 3, "l2", tuned)
+    steps = B.fwi_exec_query(grid, geom, tuned, B.WS_EXTIMAGE)["reverse_steps"]
+    b = B.extended_image(v, wav, grid, geom, d, 3, "l2", B.make_exec(tile_rows=16, reverse_steps=steps))
+    for x, y in zip(a, b):
+        assert float(x.abs().max()) > 0 and torch.equal(x, y)
