@@ -33,11 +33,11 @@ def test_tuned_calls_keep_two_steps_past_the_lds_tables(N, nrec):
 # 100 receivers, 110 samples.
 Z_SIZES = {
     "none": dict(forward=1466880, hessian=1607424, gradient=7401216, autograd=7401216, image=17650432, born=2793984,
-                 gn=8728320),
+                 gn=8728320, exact=160110080),
     "two": dict(forward=1466880, hessian=1607424, gradient=9368576, autograd=9368576, image=28603392, born=2793984,
-                gn=10302464),
+                gn=10302464, exact=160110080),
     "tuned": dict(forward=1466880, hessian=1607424, gradient=9368576, autograd=9368576, image=28603392, born=2793984,
-                  gn=10302464),
+                  gn=10302464, exact=160110080),
 }
 EXEC = {"none": {}, "two": dict(forward_steps=2, reverse_steps=2), "tuned": dict(autotune=1)}
 
@@ -64,6 +64,7 @@ def test_workspaces_of_the_z_sweeps_sizes_are_accepted(ex):
         "image": lambda: B.fwi_extended_image(*a, p, "int", p, None, 4, p, p, 16, stream=0),
         "born": lambda: B.fwi_born(*a, p, p, p, 16, stream=0),
         "gn": lambda: B.fwi_gn_hvp(*a, p, "int", p, p, p, 16, stream=0),
+        "exact": lambda: B.fwi_offset_diag_exact(*a, 4, 30.0, 0, p, p, 16, stream=0),
     }
     for name, call in calls.items():
         assert needed(call) <= Z_SIZES[ex][name], name

@@ -115,3 +115,30 @@ def test_tuned_image_past_the_lds_resident_sizes():
     b = B.extended_image(v, wav, grid, geom, d, 3, "l2", B.make_exec(tile_rows=16, reverse_steps=steps))
     for x, y in zip(a, b):
         assert float(x.abs().max()) > 0 and torch.equal(x, y)
+
+
+def test_exact_diagonal_in_workspaces_short_of_the_reported_size():
+    """Any size from the one-step z sweeps' on is accepted (the calls then run
+    those: the same bits); less is refused, and so is the reported size short
+    of less than an alignment unit."""
+    grid = Grid(40, 70, 10.0, 1e-3, 100, 8, 2300.0)
+    ix = np.arange(0, 70, 14, dtype=np.int32)
+    geom = Geometry(np.full(2, 3, np.int32), np.array([5, 60], np.int32), np.arange(3, dtype=np.int32) * len(ix),
+                    np.full(2 * len(ix), 1, np.int32), np.tile(ix, 2), np.full(2, 100, np.int32))
+    v = gaussian_anomaly(40, 70, 2000.0, 0.12, 9.0)
+    wav = ricker(14.0, 1e-3, 100).astype(np.float32)
+    full = B.fwi_offset_diag_exact_workspace_bytes(grid, geom, None, 3, 60.0)
+
+    def call(n):
+        return B.offset_diag_exact(v, wav, grid, geom, 3, 60.0, None, ws=torch.empty(n, dtype=torch.uint8, device="cuda"))
+    with pytest.raises(B.FwiError) as e:
+        call(16)
+    least = int(re.search(r"need (\d+)", str(e.value)).group(1))
+    assert least < full - 512
+    ref = call(full)
+    for n in (least, least + 1, least + 256, (least + full) // 2, full - 256, full + 100):
+        assert torch.equal(call(n), ref), n
+    for n in (least - 1, full - 255, full - 1):
+        with pytest.raises(B.FwiError) as e:
+            call(n)
+        assert e.value.code == B.FWI_ERR_WORKSPACE
