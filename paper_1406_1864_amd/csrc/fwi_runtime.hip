@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "../../include/fwi.h"
+#include "fwi_chains.h"
 #include "fwi_internal.h"
 
 namespace fwi {
@@ -201,7 +202,6 @@ std::mutex g_mutex;
 std::list<std::shared_ptr<Plan>> g_plans;  // most recent first
 std::map<std::vector<uint64_t>, ExecChoice> g_tuned;
 // launch chains of the two-step sweeps
-constexpr int kMaxBranches = 4;
 constexpr int kDefaultBranches = 2;
 
 int shot_nt(const fwi_grid* g, const fwi_geometry* geo, int s) { return geo->nt ? geo->nt[s] : g->nt_max; }
@@ -669,49 +669,41 @@ ExtArgs ext_args(const Plan& p, void* ws, int rbatch) {
   return e;
 }
 
-// Streams and events of the launch chains beside the caller's stream.  A call
-// takes a set for as long as it enqueues and gives it back; a set is reused by
-// later calls (a wait holds the state its event had when the wait was
-// enqueued), and there are as many as calls have enqueued at once per device.
-struct ChainSet {
-  int device = 0;
-  hipStream_t stream[kMaxBranches] = {};
-  hipEvent_t fork = nullptr, join[kMaxBranches] = {};
-};
-std::mutex g_chain_mutex;
-std::vector<std::unique_ptr<ChainSet>> g_chain_pool;
-
-struct Chains {
-  std::unique_ptr<ChainSet> set;
-  ~Chains() {
-    if (!set) return;
-    std::lock_guard<std::mutex> lock(g_chain_mutex);
-    g_chain_pool.push_back(std::move(set));
+struct HipChains {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  using Error = hipError_t;
+  static constexpr Error kOk = hipSuccess;
+  static Error make_stream(Stream* s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking); }
+  static Error make_event(Event* e) { return hipEventCreateWithFlags(e, hipEventDisableTiming); }
+  static bool done(Event e) {
+    const hipError_t q = hipEventQuery(e);
+    if (q != hipSuccess) (void)hipGetLastError();  // (not ready is no error of a later call)
+    return q == hipSuccess;
   }
-  // a set of the current device with n - 1 streams
-  hipError_t take(int n) {
+  static bool shared(Stream s) { return s != hipStreamPerThread; }
+};
+ChainPool<HipChains>& chain_pool() {
+  static auto* pool = new ChainPool<HipChains>;  // never destroyed
+  return *pool;
+}
+
+// a set of the current device for as long as a call enqueues
+struct Chains {
+  ChainPool<HipChains>::Set* set = nullptr;
+  ~Chains() {
+    if (set) chain_pool().give(set);
+  }
+  hipError_t take(hipStream_t user, int n) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    {
-      std::lock_guard<std::mutex> lock(g_chain_mutex);
-      for (auto it = g_chain_pool.begin(); it != g_chain_pool.end(); ++it)
-        if ((*it)->device == dev) {
-          set = std::move(*it);
-          g_chain_pool.erase(it);
-          break;
-        }
-    }
-    if (!set) {
-      set = std::make_unique<ChainSet>();
-      set->device = dev;
-    }
-    if (!set->fork && (e = hipEventCreateWithFlags(&set->fork, hipEventDisableTiming)) != hipSuccess) return e;
-    for (int i = 1; i < n; ++i) {
-      if (!set->stream[i] && (e = hipStreamCreateWithFlags(&set->stream[i], hipStreamNonBlocking)) != hipSuccess) return e;
-      if (!set->join[i] && (e = hipEventCreateWithFlags(&set->join[i], hipEventDisableTiming)) != hipSuccess) return e;
-    }
-    return hipSuccess;
+    // (queries and creation leave a capture of another stream alone)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if ((e = hipThreadExchangeStreamCaptureMode(&mode)) != hipSuccess) return e;
+    e = chain_pool().take(dev, user, n, &set);
+    const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+    return e != hipSuccess ? e : back;
   }
 };
 
@@ -787,7 +779,8 @@ int run_steps(Plan& p, void* ws, int batch, int phase, int flags, int nsteps, co
   // Launches of the two-step sweeps as independent chains over shares of the
   // slots, each on a stream of its own between a fork and a join, so that one
   // chain's launches fill the others' tails.  One chain where the caller asks
-  // for none (graph_steps = -1) or captures the call.
+  // for none (graph_steps = -1) or captures the call, or where every set of
+  // side streams is busy.
   int nbr = two && p.graph_steps > 0 ? std::max(1, std::min({p.branches, a.S, kMaxBranches})) : 1;
   if (nbr > 1) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -796,7 +789,10 @@ int run_steps(Plan& p, void* ws, int batch, int phase, int flags, int nsteps, co
   Chains chains;
   StepArgs ab[kMaxBranches];
   hipStream_t sb[kMaxBranches] = {stream};
-  if (nbr > 1) HIP_TRY(chains.take(nbr));
+  if (nbr > 1) {
+    HIP_TRY(chains.take(stream, nbr));
+    if (!chains.set) nbr = 1;  // every set is busy
+  }
   for (int i = 0; i < nbr; ++i) {
     const int s0 = a.S * i / nbr, s1 = a.S * (i + 1) / nbr;
     ab[i] = nbr > 1 ? slot_range(a, s0, s1 - s0) : a;

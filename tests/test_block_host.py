@@ -1,5 +1,5 @@
-"""Host checks of what the LDS-resident sweeps compute with (no GPU needed):
-the sponge's quotient compiled for the host against the division."""
+"""Host checks of the runtime's parts that need no GPU, compiled for the host:
+the sponge's quotient against the division, the pool of side streams."""
 import os
 import subprocess
 
@@ -57,4 +57,97 @@ def compiled(tmp_path, name, source):
 def test_sponge_quotient_is_the_division(tmp_path):
     """Finite quotients, infinities, NaN and signed zeros, bit for bit."""
     r = subprocess.run([compiled(tmp_path, "quotient", QUOTIENT)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+CHAINS = r"""
+#include <atomic>
+#include <cstdio>
+#include <set>
+#include <thread>
+#include "fwi_chains.h"
+static std::atomic<int> made{0};
+static std::atomic<bool> finished[256];  // by event
+struct Api {
+  using Stream = int;
+  using Event = int;
+  using Error = int;
+  static constexpr int kOk = 0;
+  static int make_stream(int* s) { *s = 1000 + made++; return 0; }
+  static int make_event(int* e) { *e = made++; finished[*e] = true; return 0; }
+  static bool done(int e) { return finished[e]; }
+  static bool shared(int s) { return s != 2; }
+};
+using Pool = fwi::ChainPool<Api>;
+static int failures = 0;
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); ++failures; } } while (0)
+// a call of n chains: takes a set, records its joins and gives it back
+static Pool::Set* call(Pool& p, int dev, int user, int n, bool done) {
+  Pool::Set* s = nullptr;
+  CHECK(p.take(dev, user, n, &s) == 0);
+  if (!s) return s;
+  CHECK(s->streams >= n);
+  for (int i = 1; i < n; ++i) finished[s->join[i]] = done;
+  p.give(s);
+  return s;
+}
+int main() {
+  {
+    Pool p;
+    Pool::Set* a = call(p, 0, 10, 2, false);
+    CHECK(call(p, 0, 10, 3, false) == a);          // its own stream's next call
+    Pool::Set* b = call(p, 0, 11, 2, false);       // another stream, a's work still running
+    CHECK(b && b != a);
+    for (int i = 1; i < 3; ++i) CHECK(b->stream[1] != a->stream[i]);
+    CHECK(call(p, 1, 12, 2, true)->device == 1);   // another device
+    finished[a->join[1]] = true;
+    Pool::Set* c = call(p, 0, 13, 2, false);       // one of a's two chains still runs
+    CHECK(c != a && c != b);
+    finished[a->join[1]] = finished[a->join[2]] = true;
+    CHECK(call(p, 0, 14, 2, true) == a);           // done: anyone's
+    CHECK(call(p, 0, 11, 2, false) == b);
+  }
+  {
+    Pool p;                                        // a handle that names a stream per thread
+    Pool::Set* a = call(p, 0, 2, 2, false);
+    CHECK(call(p, 0, 2, 2, false) != a);
+  }
+  {
+    Pool p;                                        // bounded: then one chain
+    std::set<Pool::Set*> seen;
+    for (int u = 0; u < fwi::kMaxChainSets; ++u) seen.insert(call(p, 0, 100 + u, 2, false));
+    CHECK((int)seen.size() == fwi::kMaxChainSets && !seen.count(nullptr));
+    CHECK(call(p, 0, 99, 2, false) == nullptr);
+    CHECK(call(p, 0, 100, 2, false) != nullptr);
+    CHECK(call(p, 1, 99, 2, true) != nullptr);
+  }
+  {
+    Pool p;                                        // no set is two calls' at once
+    std::atomic<int> held[2 * fwi::kMaxChainSets + 1] = {};
+    std::atomic<int> shared{0}, none{0};
+    std::vector<std::thread> t;
+    for (int u = 0; u < 6; ++u)
+      t.emplace_back([&, u] {
+        for (int i = 0; i < 2000; ++i) {
+          Pool::Set* s = nullptr;
+          p.take(0, 10 + u % 3, 2, &s);
+          if (!s) { ++none; continue; }
+          const int id = s->join[1] % (2 * fwi::kMaxChainSets + 1);
+          if (held[id]++) ++shared;
+          held[id]--;
+          p.give(s);
+        }
+      });
+    for (auto& x : t) x.join();
+    CHECK(shared == 0 && none == 0);
+  }
+  return failures != 0;
+}
+"""
+
+
+def test_side_streams_of_busy_calls_are_not_shared(tmp_path):
+    """A set of side streams goes to another stream's call only when its work
+    is done; there is a bound on the sets of a device."""
+    r = subprocess.run([compiled(tmp_path, "chains", CHAINS)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
