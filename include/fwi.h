@@ -157,9 +157,11 @@ typedef struct {
                                  workgroup tiling; u[n+1], u[n+2], d[n+2]
                                  written once per two steps); 0 = tuned, else
                                  by size (1 where a z-sweep field is set).  Not
-                                 used with a free surface, in plain mode or for
-                                 Born modelling; the forward-only calls choose
-                                 by themselves                                 */
+                                 used with a free surface or in plain mode, nor
+                                 by the other calls: modelling, fwi_misfit_value
+                                 and fwi_hessian_diag choose by themselves,
+                                 Born modelling and Gauss-Newton products have
+                                 one-step and LDS-resident sweeps              */
     int32_t graph_branches;   /* independent launch chains of the two-step
                                  sweeps, each over a contiguous share of the
                                  launch's shots on a stream of its own between
@@ -199,9 +201,18 @@ size_t fwi_workspace_bytes(const fwi_grid *grid, const fwi_geometry *geom,
 /* The execution settings (shots_in_flight, tile_rows, graph_steps, prefetch,
  * prefetch_reverse, shots_in_flight_reverse, tile_rows_reverse,
  * reverse_steps, forward_steps, graph_branches) that a
- * call with these arguments uses: the autotuned choice once tuning has run on
- * the current device, else the heuristic defaults.  Fills *chosen (mode and
- * autotune copied from exec).  Returns 0 or FWI_ERR_*. */
+ * call with these arguments uses in a workspace of the reported size: the
+ * autotuned choice once tuning has run on the current device, else the
+ * heuristic defaults.  forward_steps or reverse_steps 0 says that the sweep is
+ * LDS-resident.  Of an untuned call, tile rows and prefetch are 0 as well
+ * where naming them would choose another sweep (LDS-resident ones, and two
+ * steps per launch of the calls that choose them by themselves), so that the
+ * settings passed back in choose the same sweeps (two reverse steps named that
+ * way bring an even snapshot spacing); of a tuned call they are those of the
+ * tuning entry, which an LDS-resident sweep does not use.  (forward_steps is 1
+ * instead of 0 where exec names the field in a call that does not use it.)
+ * Fills *chosen (mode and autotune copied from exec).
+ * Returns 0 or FWI_ERR_*. */
 int fwi_exec_query(const fwi_grid *grid, const fwi_geometry *geom, const fwi_exec *exec,
                    int what, fwi_exec *chosen);
 

@@ -965,6 +965,8 @@ int check_outputs_hess(int hmax, int rcv_model, float* D, const fwi_grid* g) {
 }
 
 // ---------------------------------------------------------------- autotuner
+int named_forward_steps(const fwi_exec* ex, int what);
+
 double time_steps(Plan& p, void* ws, int flags, int phase, int nsteps, const float* wavelet,
                   int64_t wstride, hipStream_t s) {
   hipEvent_t e0, e1;
@@ -1022,10 +1024,9 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   // forward time steps per launch: two for the gradient's forward sweep
   // (not the Born one), tried first so that near-ties keep the fewer bytes
   std::vector<int> FSs;
-  if (ex && ex->forward_steps > 0) FSs = {ex->forward_steps};
+  if (named_forward_steps(ex, what) > 0) FSs = {ex->forward_steps};
   else if (g->free_surface || what == FWI_WS_BORN || what == FWI_WS_GNHVP) FSs = {1};
   else FSs = {2, 1};
-  if (!grad && ex && ex->forward_steps > 0) FSs = {1};  // (the field is the gradient's)
   const int fwd_flags = grad ? (kFwdRecord | kFwdCkpt) : (what == FWI_WS_HESSIAN ? kFwdIllum : kFwdRecord);
   const int nsteps = 32;  // launches timed per candidate
   // FWI_TUNE_LOG set: each candidate's best time goes to stderr
@@ -1179,18 +1180,25 @@ struct CallCtx {
   std::shared_ptr<Plan> plan;
 };
 
+bool forward_only(int what) { return what == FWI_WS_FORWARD || what == FWI_WS_HESSIAN || what == FWI_WS_BORN; }
+
+// exec's forward_steps where the call uses the field
+int named_forward_steps(const fwi_exec* ex, int what) {
+  return ex && (what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE) ? ex->forward_steps : 0;
+}
+
 // The LDS-resident sweeps stand in for the z sweeps unless the caller sets
 // what only the z sweeps have: rows per tile, prefetch, steps per launch.
-int blk_allowed(const fwi_exec* ex) {
+int blk_allowed(const fwi_exec* ex, int what) {
   if (!ex) return 3;
   if (ex->mode == FWI_EXEC_PLAIN) return 0;
   int blk = 3;
-  if (ex->tile_rows > 0 || ex->prefetch > 0 || ex->forward_steps > 0) blk &= ~1;
+  if (ex->tile_rows > 0 || ex->prefetch > 0 || named_forward_steps(ex, what) > 0) blk &= ~1;
   if (ex->tile_rows > 0 || ex->tile_rows_reverse > 0 || ex->prefetch_reverse > 0 || ex->reverse_steps > 0) blk &= ~2;
   return blk;
 }
 
-ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex) {
+ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what) {
   ExecChoice c{};
   const int Z = g->nz + 2 * g->nsponge;
   c.S = (ex && ex->shots_in_flight > 0) ? ex->shots_in_flight : default_shots_in_flight(geo->nshot);
@@ -1201,9 +1209,9 @@ ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exe
   c.Sr = (ex && ex->shots_in_flight_reverse > 0) ? ex->shots_in_flight_reverse : 0;
   c.TZr = (ex && ex->tile_rows_reverse > 0) ? ex->tile_rows_reverse : 0;
   c.rsteps = (ex && ex->reverse_steps > 0) ? ex->reverse_steps : 1;
-  c.fsteps = (ex && ex->forward_steps > 0) ? ex->forward_steps : 1;
+  c.fsteps = std::max(named_forward_steps(ex, what), 1);
   c.branches = (ex && ex->graph_branches > 0) ? ex->graph_branches : kDefaultBranches;
-  c.blk = blk_allowed(ex);
+  c.blk = blk_allowed(ex, what);
   return c;
 }
 
@@ -1219,7 +1227,7 @@ ExecChoice base_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exe
 // 31.9, 39.7, 64.3 | 87.6, Born 33.8, 32.9, 46.0, 77.4 | 88.1; 32 shots: 58.7,
 // 51.2, 56.7, 57.7 | 96.1, 119, 120, 128, 131 | 169, 154, 154, 159, 159 | 175).
 void untuned_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, ExecChoice& c) {
-  const int autos = blk_allowed(ex);
+  const int autos = blk_allowed(ex, what);
   if (!autos || geo->nshot == 0) return;
   const int runs = std::max(1, std::min(c.S, geo->nshot));
   const int64_t cells = (int64_t)runs * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
@@ -1237,8 +1245,6 @@ void untuned_choice(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* 
   }
 }
 
-bool forward_only(int what) { return what == FWI_WS_FORWARD || what == FWI_WS_HESSIAN || what == FWI_WS_BORN; }
-
 // Shots in flight that a tuned call is sized for and that the LDS-resident
 // sweeps take.
 int tuned_runs(const fwi_geometry* geo) { return std::min(std::max(geo->nshot, 1), 64); }
@@ -1246,8 +1252,8 @@ int tuned_runs(const fwi_geometry* geo) { return std::min(std::max(geo->nshot, 1
 // The sweeps of an autotuned call that run LDS-resident (bits of blk_takes).
 // The tuned shots in flight are the z sweeps': whether the LDS-resident ones
 // take over is decided for every shot at once, which suits them best.
-int tuned_blk(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex) {
-  return ex->shots_in_flight > 0 ? 0 : blk_allowed(ex) & blk_takes(g, geo, tuned_runs(geo));
+int tuned_blk(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what) {
+  return ex->shots_in_flight > 0 ? 0 : blk_allowed(ex, what) & blk_takes(g, geo, tuned_runs(geo));
 }
 // whether that is every sweep of the call: nothing is left to time
 bool nothing_to_tune(int blk, int what) { return blk == 3 || ((blk & 1) && forward_only(what)); }
@@ -1342,9 +1348,6 @@ void cache_store(const std::vector<uint64_t>& k, const ExecChoice& c) {
   fclose(f);
 }
 
-// Returns the plan for a call; with autotuning requested and no cached
-// choice, runs the tuner inside `ws` first (needs a workspace sized for the
-// untuned maximum, which fwi_workspace_bytes reports).
 int check_exec(const fwi_exec* ex) {
   if (ex && ex->mode != FWI_EXEC_PLAIN && ex->mode != FWI_EXEC_BATCHED) return fail(FWI_ERR_ARG, "bad exec mode");
   if (ex && (ex->shots_in_flight < 0 || ex->tile_rows < 0 || ex->graph_steps < -1 ||
@@ -1395,25 +1398,36 @@ int ws_check(const Plan& p, size_t ws_bytes) {
   return ws_bytes < p.L.total ? ws_short(ws_bytes, p.L.total) : FWI_OK;
 }
 
+// Returns the plan for a call; with autotuning requested and no cached
+// choice, runs the tuner inside `ws` first (needs a workspace sized for the
+// untuned maximum, which fwi_workspace_bytes reports).
+enum class Want {
+  kRun,   // the call's plan
+  kSize,  // one of the size that the call may need; nothing is looked up or timed
+  kQuery  // the call's plan in the workspace it is sized for, as far as known without timing
+};
 int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int what, void* ws,
              size_t ws_bytes, const float* v, const float* wavelet, int64_t wstride, hipStream_t s,
-             std::shared_ptr<Plan>& out, bool sizing_only, int ext_h = -1, bool compact = false) {
+             std::shared_ptr<Plan>& out, Want want, int ext_h = -1, bool compact = false,
+             ExecChoice* chosen = nullptr) {
   const int plain = ex && ex->mode == FWI_EXEC_PLAIN;
   if (int rc = check_exec(ex)) return rc;
-  ExecChoice c = base_choice(g, geo, ex);
+  const bool sizing_only = want == Want::kSize;
+  ExecChoice c = base_choice(g, geo, ex, what);
   const int branches = c.branches, blk = c.blk;  // not tuned: the tuner times with the former, without the latter
   const bool tuned_call = !plain && ex && ex->autotune;
   const uint64_t ikey = inputs_hash(g, geo);
   std::lock_guard<std::mutex> lock(g_mutex);
+  const ExecChoice untuned = c;
   if (tuned_call) {
     // the workspace is sized for the largest candidate
     if (!(ex->shots_in_flight > 0)) c.S = tuned_runs(geo);
     if (!(ex->tile_rows > 0)) c.TZ = 32;
     c.Sr = 0;  // reverse buffers sized for the forward's maximum
     if (!(ex->reverse_steps > 0)) c.rsteps = 2;  // and for the two-step sweeps' levels
-    if (!(ex->forward_steps > 0)) c.fsteps = 2;
+    if (!(named_forward_steps(ex, what) > 0)) c.fsteps = 2;
   }
-  const int resident = tuned_call ? tuned_blk(g, geo, ex) : 0;
+  const int resident = tuned_call ? tuned_blk(g, geo, ex, what) : 0;
   ExecChoice tuned;
   // compact: what a workspace of the one-step z sweeps' (tuned calls: the z
   // sweeps') size holds
@@ -1456,7 +1470,7 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
     }
     out = build_plan(g, geo, c, plain, what, key, ext_h);
     out->ikey = ikey;
-    if (!sizing_only && out->L.total <= ws_bytes) {
+    if (want == Want::kRun && out->L.total <= ws_bytes) {
       g_plans.push_front(out);
       while (g_plans.size() > 16) g_plans.pop_back();
     }
@@ -1470,6 +1484,10 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
       t = it->second;
     } else {
       if (!(cache_lookup(tk, t) && t.S <= tuned.S && t.Sr <= tuned.S)) {
+        if (want == Want::kQuery) {
+          tuned = untuned;
+          return FWI_OK;
+        }
         t = tuned;
         if (untimed) {
           t = c;
@@ -1480,16 +1498,18 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
         }
         cache_store(tk, t);
       }
-      g_tuned[tk] = t;
+      if (want == Want::kRun) g_tuned[tk] = t;
     }
-    if (!untimed) {
+    if (!untimed || want == Want::kQuery) {
       tuned = t;
       tuned.branches = branches;
     }
     return FWI_OK;
   };
   tuned = c;
-  if (tuned_call && !sizing_only) {
+  if (tuned_call && want == Want::kQuery) {
+    if (int rc = look_up(nothing_to_tune(resident, what))) return rc;
+  } else if (tuned_call && want == Want::kRun) {
     if (nothing_to_tune(resident, what)) {
       // 150 to 290 ms of candidates in a first call that takes 2 to 3 ms (3
       // shots of 200 x 90 cells, 16 of 256 x 96) had no part in what ran
@@ -1501,10 +1521,11 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   }
   settle(compact);
   find_or_build();
-  if (!sizing_only && out->L.total > ws_bytes) {
+  if (want == Want::kRun && out->L.total > ws_bytes) {
     settle(true);
     find_or_build();
   }
+  if (chosen) *chosen = c;
   return FWI_OK;
 }
 
@@ -1516,7 +1537,7 @@ int size_check(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, i
   size_t need = SIZE_MAX;
   for (bool compact : {false, true}) {
     std::shared_ptr<Plan> p;
-    if (int rc = get_plan(g, geo, ex, what, nullptr, 0, nullptr, nullptr, 0, nullptr, p, true, ext_h, compact)) return rc;
+    if (int rc = get_plan(g, geo, ex, what, nullptr, 0, nullptr, nullptr, 0, nullptr, p, Want::kSize, ext_h, compact)) return rc;
     need = std::min(need, p->L.total);
     if (ws_bytes >= need) return FWI_OK;
   }
@@ -1641,7 +1662,7 @@ ExecChoice dx_choice(const fwi_grid* g, const fwi_geometry* side, const fwi_exec
   const int TZ = (ex && ex->tile_rows > 0) ? ex->tile_rows : default_tile_rows(Z);
   const int pf = (ex && ex->prefetch > 0) ? ex->prefetch : 1;
   ExecChoice c{S, TZ, 0, pf, 1, S, TZ, 1, 1};
-  c.blk = compact ? 0 : blk_allowed(ex) & 1;
+  c.blk = compact ? 0 : blk_allowed(ex, FWI_WS_FORWARD) & 1;
   c.act = compact ? 0 : 1;
   const int64_t cells = (int64_t)S * (g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
   if (c.blk && !(blk_takes(g, side, S) & 1)) {
@@ -1754,39 +1775,30 @@ int fwi_exec_query(const fwi_grid* grid, const fwi_geometry* geom, const fwi_exe
   if (what < FWI_WS_FORWARD || what > FWI_WS_GNHVP || what == FWI_WS_PRECOND)
     return fail(FWI_ERR_ARG, "bad `what`");
   const int plain = exec && exec->mode == FWI_EXEC_PLAIN;
-  ExecChoice c = base_choice(grid, geom, exec);
-  if (!plain && !(exec && exec->autotune)) untuned_choice(grid, geom, exec, what, c);
-  if (!plain && exec && exec->autotune) {
-    std::lock_guard<std::mutex> lock(g_mutex);
-    const std::vector<uint64_t> tk =
-        tune_key(grid, geom, exec, what, nothing_to_tune(tuned_blk(grid, geom, exec), what));
-    auto it = g_tuned.find(tk);
-    ExecChoice t{};
-    if (it != g_tuned.end()) {
-      c = it->second;
-    } else if (cache_lookup(tk, t) && t.S <= c.S && t.Sr <= c.S) {
-      c = t;
-    }
-  }
+  ExecChoice c;
+  std::shared_ptr<Plan> p;
+  if ((rc = get_plan(grid, geom, exec, what, nullptr, 0, nullptr, nullptr, 0, nullptr, p, Want::kQuery, -1, false, &c)))
+    return rc;
+  const bool tuned = exec && exec->autotune;
   chosen->mode = exec ? exec->mode : FWI_EXEC_BATCHED;
   chosen->autotune = exec ? exec->autotune : 0;
-  chosen->shots_in_flight = plain ? 1 : std::max(1, std::min(c.S, std::max(geom->nshot, 1)));
-  chosen->tile_rows = c.TZ;
-  chosen->graph_steps = plain ? -1 : c.graph_steps;
-  chosen->prefetch = c.pf_fwd;
-  chosen->prefetch_reverse = c.pf_rev;
-  {
-    // the reverse sweep's settings as build_plan resolves them
-    chosen->shots_in_flight_reverse =
-        resolve_sr(chosen->shots_in_flight, c.Sr, plain, what == FWI_WS_AUTOGRAD, geom->nshot);
-    chosen->tile_rows_reverse = c.TZr > 0 ? c.TZr : c.TZ;
-    chosen->reverse_steps = (plain || grid->free_surface) ? 1 : c.rsteps;
-    chosen->forward_steps = (plain || grid->free_surface || what == FWI_WS_FORWARD || what == FWI_WS_HESSIAN ||
-                             what == FWI_WS_BORN || what == FWI_WS_GNHVP)
-                                ? 1
-                                : c.fsteps;
-    chosen->graph_branches = plain ? 1 : (exec && exec->graph_branches > 0 ? exec->graph_branches : kDefaultBranches);
-  }
+  chosen->shots_in_flight = p->S;
+  chosen->graph_steps = p->graph_steps;
+  chosen->shots_in_flight_reverse = p->Sr;
+  chosen->graph_branches = plain ? 1 : p->branches;
+  // An LDS-resident sweep has 0 steps.  Rows and prefetch are 0 where naming
+  // them would choose another sweep than the one that runs, unless the call is
+  // a tuned one, whose entry is reported as it stands.
+  const bool lds_f = p->bf.T > 0, lds_r = p->br.T > 0;
+  const bool by_size = !tuned && (lds_f || (p->fwd_steps == 2 && forward_only(what)));
+  chosen->forward_steps = !lds_f ? p->fwd_steps
+                          : exec && exec->forward_steps > 0 ? 1  // named, though the call does not use the field
+                                                            : 0;
+  chosen->reverse_steps = lds_r ? 0 : p->rev_steps;
+  chosen->tile_rows = by_size ? 0 : c.TZ;
+  chosen->prefetch = by_size ? 0 : c.pf_fwd;
+  chosen->tile_rows_reverse = lds_r && !tuned ? 0 : c.TZr > 0 ? c.TZr : c.TZ;
+  chosen->prefetch_reverse = lds_r && !tuned ? 0 : c.pf_rev;
   return FWI_OK;
 }
 
@@ -1803,7 +1815,7 @@ size_t fwi_workspace_bytes(const fwi_grid* grid, const fwi_geometry* geom, const
     return 0;
   }
   std::shared_ptr<Plan> p;
-  if (get_plan(grid, geom, exec, what, nullptr, 0, nullptr, nullptr, 0, nullptr, p, true,
+  if (get_plan(grid, geom, exec, what, nullptr, 0, nullptr, nullptr, 0, nullptr, p, Want::kSize,
                what == FWI_WS_EXTIMAGE ? hmax : -1))
     return 0;
   return p->L.total;
@@ -1819,7 +1831,7 @@ static int forward_impl(const fwi_grid* grid, const fwi_geometry* geom, const fw
   const int what = dv ? FWI_WS_BORN : FWI_WS_FORWARD;
   std::shared_ptr<Plan> p;
   if ((rc = size_check(grid, geom, exec, what, ws_bytes))) return rc;
-  if ((rc = get_plan(grid, geom, exec, what, workspace, ws_bytes, v, wavelet, wavelet_stride, s, p, false)))
+  if ((rc = get_plan(grid, geom, exec, what, workspace, ws_bytes, v, wavelet, wavelet_stride, s, p, Want::kRun)))
     return rc;
   if ((rc = ws_check(*p, ws_bytes))) return rc;
   if (geom->nshot == 0) return FWI_OK;
@@ -1852,7 +1864,7 @@ int fwi_misfit_value(const fwi_grid* grid, const fwi_geometry* geom, const fwi_e
   std::shared_ptr<Plan> p;
   if ((rc = size_check(grid, geom, exec, FWI_WS_FORWARD, ws_bytes))) return rc;
   if ((rc = get_plan(grid, geom, exec, FWI_WS_FORWARD, workspace, ws_bytes, v, wavelet, wavelet_stride, s, p,
-                     false)))
+                     Want::kRun)))
     return rc;
   if ((rc = ws_check(*p, ws_bytes))) return rc;
   if ((rc = begin_call(*p, workspace, v, s))) return rc;
@@ -1919,7 +1931,7 @@ static int gradient_impl(const fwi_grid* grid, const fwi_geometry* geom, const f
       }
     if (!p) return fail(FWI_ERR_STATE, "fwi_misfit_backward without a matching fwi_misfit_forward");
   } else {
-    if ((rc = get_plan(grid, geom, exec, what, ws, ws_bytes, v, wavelet, wstride, s, p, false, ext_h))) return rc;
+    if ((rc = get_plan(grid, geom, exec, what, ws, ws_bytes, v, wavelet, wstride, s, p, Want::kRun, ext_h))) return rc;
   }
   if ((rc = ws_check(*p, ws_bytes))) return rc;
   const Plan& cp = *p;
@@ -2054,7 +2066,7 @@ int fwi_hessian_diag(const fwi_grid* grid, const fwi_geometry* geom, const fwi_e
   std::shared_ptr<Plan> p;
   if ((rc = size_check(grid, geom, exec, FWI_WS_HESSIAN, ws_bytes))) return rc;
   if ((rc = get_plan(grid, geom, exec, FWI_WS_HESSIAN, workspace, ws_bytes, v, wavelet, wavelet_stride, s, p,
-                     false)))
+                     Want::kRun)))
     return rc;
   if ((rc = ws_check(*p, ws_bytes))) return rc;
   const size_t model_bytes = sizeof(float) * p->d.model;

@@ -76,3 +76,56 @@ def test_tuned_image_is_sized_for_two_steps_per_launch():
     grid, geom = problem(1000, 400, 20, 4, 50)
     two = B.fwi_workspace_bytes(grid, geom, B.make_exec(forward_steps=2, reverse_steps=2), B.WS_EXTIMAGE, 3)
     assert B.fwi_workspace_bytes(grid, geom, B.make_exec(autotune=1), B.WS_EXTIMAGE, 3) >= two
+
+
+@pytest.mark.parametrize("nx,nz,N,ns,nrec,fs,what,steps,shots", [
+    (300, 150, 20, 9, 1024, False, B.WS_GRADIENT, (0, 0), 8),
+    (300, 150, 20, 9, 1025, False, B.WS_GRADIENT, (2, 2), 8),    # receivers of a shot
+    (300, 150, 128, 2, 30, False, B.WS_GRADIENT, (0, 0), 2),
+    (300, 150, 129, 2, 30, False, B.WS_GRADIENT, (2, 2), 2),     # sponge cells
+    (960, 360, 20, 4, 30, False, B.WS_GRADIENT, (0, 0), 4),      # 1.6 M cells a step
+    (961, 360, 20, 4, 30, False, B.WS_GRADIENT, (0, 2), 4),
+    (961, 360, 20, 4, 30, False, B.WS_GNHVP, (0, 2), 4),
+    (961, 360, 20, 4, 30, True, B.WS_GRADIENT, (0, 1), 4),       # no two steps with a free surface
+    (960, 360, 20, 20, 30, False, B.WS_FORWARD, (0, 1), 16),
+    (961, 360, 20, 24, 30, False, B.WS_FORWARD, (2, 1), 24),     # 8 M cells a step
+    (961, 360, 20, 24, 30, False, B.WS_HESSIAN, (2, 1), 24),
+    (961, 360, 20, 24, 30, False, B.WS_BORN, (1, 1), 24),
+    (961, 360, 20, 24, 30, False, B.WS_AUTOGRAD, (2, 2), 24),
+])
+def test_query_reports_the_sweeps_that_run(nx, nz, N, ns, nrec, fs, what, steps, shots):
+    """Steps per launch on both sides of each limit (0: LDS-resident); the
+    settings passed back in choose the same sweeps."""
+    grid, geom = problem(nx, nz, N, ns, nrec, fs=fs)
+    q = B.fwi_exec_query(grid, geom, None, what)
+    assert (q["forward_steps"], q["reverse_steps"], q["shots_in_flight"]) == (*steps, shots)
+    # rows and prefetch: 0 where naming them would choose another sweep
+    free = steps[0] == 0 or (steps[0] == 2 and what in (B.WS_FORWARD, B.WS_HESSIAN))
+    assert (q["tile_rows"] == 0) == free and (q["prefetch"] == 0) == free
+    assert (q["tile_rows_reverse"] == 0) == (steps[1] == 0) and (q["prefetch_reverse"] == 0) == (steps[1] == 0)
+    assert B.fwi_exec_query(grid, geom, B.make_exec(**q), what) == q
+
+
+def test_query_of_tuned_calls_takes_every_shot_where_lds_resident():
+    """Without a tuning entry: what is fixed by the sizes alone."""
+    tuned = B.make_exec(autotune=1)
+    grid, geom = problem(130, 90, 11, 40, 30)
+    for what in (B.WS_FORWARD, B.WS_GRADIENT, B.WS_AUTOGRAD):
+        q = B.fwi_exec_query(grid, geom, tuned, what)
+        assert q["shots_in_flight"] == 40 and q["forward_steps"] == 0, what
+    assert q["reverse_steps"] == 0 and q["shots_in_flight_reverse"] == 40
+    grid, geom = problem(130, 90, 11, 40, 1025)
+    q = B.fwi_exec_query(grid, geom, tuned, B.WS_GRADIENT)
+    assert q["shots_in_flight"] == 32 and q["forward_steps"] > 0 and q["reverse_steps"] > 0
+
+
+def test_forward_steps_are_the_gradient_calls_alone():
+    """Calls that do not use the field choose their sweeps as if it were 0,
+    tuned or not."""
+    for nx, ns, nrec in ((130, 3, 30), (961, 24, 30), (300, 2, 1025)):
+        grid, geom = problem(nx, 360, 20, ns, nrec)
+        for what in (B.WS_FORWARD, B.WS_HESSIAN, B.WS_BORN, B.WS_GNHVP):
+            for steps in (1, 2):
+                for tuned in (0, 1):
+                    a = B.fwi_workspace_bytes(grid, geom, B.make_exec(autotune=tuned, forward_steps=steps), what)
+                    assert a == B.fwi_workspace_bytes(grid, geom, B.make_exec(autotune=tuned), what)
