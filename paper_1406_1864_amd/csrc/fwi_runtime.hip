@@ -1263,10 +1263,10 @@ std::vector<uint64_t> tune_key(const fwi_grid* g, const fwi_geometry* geo, const
   Hasher h;
   h.grid(*g);
   h.pod(geo->nshot);
-  // extended-image and Gauss-Newton calls run the gradient's sweeps, Born
-  // modelling the forward's: tune them once for each pair
-  if (what == FWI_WS_EXTIMAGE || what == FWI_WS_GNHVP) what = FWI_WS_GRADIENT;
-  if (what == FWI_WS_BORN) what = FWI_WS_FORWARD;
+  // extended-image calls run the gradient's sweeps: tuned once for both.  (Born
+  // modelling and Gauss-Newton products have no two-step forward sweep: what
+  // one finds is not the modelling's or the gradient's best.)
+  if (what == FWI_WS_EXTIMAGE) what = FWI_WS_GRADIENT;
   std::vector<uint64_t> k = {h.h, (uint64_t)what, (uint64_t)(ex ? ex->shots_in_flight : 0),
                              (uint64_t)(ex ? ex->tile_rows : 0), (uint64_t)(ex ? ex->prefetch : 0),
                              (uint64_t)(ex ? ex->prefetch_reverse : 0),

@@ -142,3 +142,34 @@ def test_exact_diagonal_in_workspaces_short_of_the_reported_size():
         with pytest.raises(B.FwiError) as e:
             call(n)
         assert e.value.code == B.FWI_ERR_WORKSPACE
+
+
+def test_calls_with_other_candidates_are_tuned_apart(tmp_path, monkeypatch):
+    """Born modelling and Gauss-Newton products have no two-step forward sweep:
+    they neither give modelling and gradients their settings nor take theirs."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("FWI_TUNE_CACHE", str(cache))
+    nx, nz, nt = 120, 40, 41
+    grid = Grid(nz, nx, 10.0, 1e-3, nt, 131, 2300.0)   # a sponge that the LDS-resident sweeps do not hold
+    ix = np.arange(0, nx, 10, dtype=np.int32)
+    geom = Geometry(np.full(2, 3, np.int32), np.array([5, 110], np.int32), np.arange(3, dtype=np.int32) * len(ix),
+                    np.full(2 * len(ix), 1, np.int32), np.tile(ix, 2), np.full(2, nt, np.int32))
+    v = gaussian_anomaly(nz, nx, 2000.0, 0.12, 9.0)
+    dv = np.full((nz, nx), 10.0, np.float32)
+    wav = ricker(20.0, 1e-3, nt).astype(np.float32)
+    d = random_traces(geom, nt, seed=5, scale=1e-2)
+    tuned = B.make_exec(autotune=1)
+    calls = [lambda: B.born(v, wav, grid, geom, dv, tuned), lambda: B.gn_hvp(v, wav, grid, geom, dv, "int", tuned),
+             lambda: B.forward(v, wav, grid, geom, tuned), lambda: B.gradient(v, wav, grid, geom, d, "int", tuned)]
+    keys = []
+    for call in calls:
+        call()
+        lines = cache.read_text().splitlines()
+        assert len(lines) == len(keys) + 1
+        key, choice = lines[-1].split(":")
+        keys.append(key)
+        if len(keys) <= 2:
+            assert choice.split()[-1] == "1"    # forward steps
+    assert len(set(keys)) == 4
+    B.extended_image(v, wav, grid, geom, d, 2, "int", tuned)   # the gradient's candidates: its entry
+    assert len(cache.read_text().splitlines()) == 4
