@@ -561,8 +561,12 @@ def main():
                      "measured_bytes_per_cell_step": traffic / (Sr * RS * Z * X) if traffic else None,
                      "measured_GBps": traffic / (launch_us * 1e-6) / 1e9 if traffic else None},
         "copy_GBps": copy_gbs,
+        # bytes of one-step launches over every padded cell: no share of the
+        # peak where the sweep runs two steps per launch, which move about half
+        # of them, and leaves out tiles that the wavefield has not reached
         "forward_roofline": {"achieved": fwd_bytes / (phase[0] / args.steps * 1e-3) / 1e9, "unit": "GB/s",
-                             "frac": fwd_bytes / (phase[0] / args.steps * 1e-3) / 1e9 / HBM_PEAK_GBS},
+                             "frac": fwd_bytes / (phase[0] / args.steps * 1e-3) / 1e9 / HBM_PEAK_GBS
+                             if chosen["forward_steps"] == 1 else None},
     }
 
     if not args.no_plain:

@@ -112,15 +112,18 @@ typedef struct {
 typedef struct {
     int32_t mode;             /* FWI_EXEC_BATCHED (default) or FWI_EXEC_PLAIN:
                                  plain = one shot at a time, one launch per
-                                 time step, no graph, no autotuning            */
+                                 time step, no autotuning                      */
     int32_t shots_in_flight;  /* shots advanced together by one launch of the
                                  forward sweep                                 */
     int32_t tile_rows;        /* rows of one wavefront's tile (z sweep length)
                                  of the forward sweep                          */
     int32_t graph_steps;      /* launches of the one-step and two-step sweeps
                                  between two folds of the extended image
-                                 (0 = 32); -1 = every sweep as one launch
-                                 chain on the caller's stream                  */
+                                 (0 = 32; time steps, not launches, where two
+                                 steps are neither named nor tuned;
+                                 LDS-resident sweeps fold every 32 steps);
+                                 -1 = every sweep as one launch chain on the
+                                 caller's stream                               */
     int32_t autotune;         /* 1 = pick unset fields by timing a few steps
                                  of each candidate inside the call's workspace;
                                  the choice is cached per grid, geometry and
@@ -169,7 +172,8 @@ typedef struct {
                                  it, so that one chain's launches run in the
                                  others' tails: 1 to 4 (at most the shots per
                                  launch); 0 = 2; 1 while the caller's stream is
-                                 being captured                                */
+                                 being captured, and while the side streams of
+                                 8 other streams' calls are busy               */
 } fwi_exec;
 
 enum { FWI_EXEC_BATCHED = 0, FWI_EXEC_PLAIN = 1 };
@@ -192,7 +196,9 @@ enum { FWI_WS_FORWARD = 0, FWI_WS_GRADIENT = 1, FWI_WS_HESSIAN = 2,
 /* Bytes of device workspace needed by the matching entry point (hmax: offset
  * range of the offset diagonal, 0 if unused; for FWI_WS_EXTIMAGE the offset
  * range of the extended image, which sizes its buffers).  Returns 0 if the arguments fail
- * validation (see fwi_last_error).  FWI_WS_AUTOGRAD sizes the pair
+ * validation (see fwi_last_error).  A smaller workspace that holds the call's
+ * z sweeps (untuned: the one-step ones) is accepted too and runs those; a
+ * refusal names the least size.  FWI_WS_AUTOGRAD sizes the pair
  * fwi_misfit_forward / fwi_misfit_backward, which keeps the checkpoints of
  * every shot between the two calls. */
 size_t fwi_workspace_bytes(const fwi_grid *grid, const fwi_geometry *geom,
@@ -289,9 +295,9 @@ int fwi_gradient_static(const fwi_grid *grid, const fwi_geometry *geom, const fw
  * is dJ/dv.  Arguments as fwi_gradient; grad (NULL allowed) also receives
  * dJ/dv; image is [2*hmax+1][nz][nx] float, 0 <= hmax <= 32, hmax < nx.
  * Workspace: fwi_workspace_bytes(..., FWI_WS_EXTIMAGE, hmax); besides the
- * gradient's buffers it holds lam and D of the model cells for graph_steps
- * reverse steps per shot in flight (32 in plain mode and for the
- * LDS-resident sweeps). */
+ * gradient's buffers it holds lam and D of the model cells for the reverse
+ * steps between two folds (exec's graph_steps; 32 in plain mode) per shot in
+ * flight. */
 int fwi_extended_image(const fwi_grid *grid, const fwi_geometry *geom, const fwi_exec *exec,
                        const float *v, const float *wavelet, int64_t wavelet_stride,
                        const float *d_obs, int misfit, double *J, float *grad,

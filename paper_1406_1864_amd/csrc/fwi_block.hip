@@ -6,9 +6,10 @@
 // down 8 + tile rows one after the other; each row costs about 0.4 us of
 // latency, so a launch lasts 12 us on a 40 x 32 padded grid and 30 us on a
 // 240 x 140 one whatever the work in it.  Here a workgroup owns a tile and
-// computes every cell of it at once: a step is one pass of 20 vector
-// operations per cell between two barriers, and T steps share one launch and
-// one read and write of the fields.
+// computes every cell of it at once: a step is one pass over its cells to a
+// barrier (two where LDS holds the fields once: two rows of both fields or of
+// Born modelling per thread, four rows), and T steps share one launch and one
+// read and write of the fields.
 //
 // Tiling.  A workgroup computes a region of RX x RZ cells.  The tile it owns
 // is the region without a margin of 4 T cells on the sides where the grid
@@ -26,14 +27,15 @@
 // give the same bits (the damped cells' FP64 division by 1 + g is a product
 // with its reciprocal and one correction, which rounds the same).
 //
-// What bounds it: vector instructions (22 per cell for the Laplacian with the
-// neighbour lanes' DPP moves, about 28 in all; 54 of 64 lane-operations per
-// clock and CU measured for plain FMAs) times the margin's repeated cells, and
-// 6 us (forward) or 8 us (reverse) of launch, load and store per T steps.
+// What bounds it: vector instructions (20 for a cell's Laplacian, 2 moves from
+// the neighbouring lanes, the update, in the sponge in FP64; 54 of 64
+// lane-operations per clock and CU measured for plain FMAs) times the margin's
+// repeated cells, and 6 us (forward) or 8 us (reverse) of launch, load and
+// store per T steps.
 // Measured per time step, forward / reverse, against the one-step z sweeps
 // with their default 16- to 64-row tiles: 1 shot of 240 x 140 cells 2.3 / 3.6
 // us (27 / 31), 16 shots of 288 x 128 4.0 / 7.4 us (24 / 30), 4 shots of
-// 1088 x 448 11 / 22 us (56 / 61); a 40 x 32 grid 1.2 / 1.6 us (12 / 16).
+// 1088 x 448 11 / 20 us (56 / 61); a 40 x 32 grid 1.2 / 1.6 us (12 / 16).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -403,8 +403,7 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   const int ns = geo->nshot;
   p->ntrace = ns > 0 ? geo->rec_ptr[ns] : 0;
   p->trace_shot.assign(std::max(p->ntrace, 1), 0);
-  // (also where tuning may yet choose such a sweep: the size it is given)
-  if (!plain && ((ex.blk & blk_takes(g, geo, p->S) & 1) || (grad && (ex.blk & blk_takes(g, geo, p->Sr) & 2)))) {
+  if (p->bf.T || p->br.T) {
     p->rcell.assign(std::max(p->ntrace, 1), make_int2(0, 0));
     for (int r = 0; r < p->ntrace; ++r) p->rcell[r] = make_int2(geo->rec_iz[r] + d.N, geo->rec_ix[r] + d.mx0);
   }
@@ -560,9 +559,12 @@ std::shared_ptr<Plan> build_plan(const fwi_grid* g, const fwi_geometry* geo, con
   L.rrows2 = take(sizeof(RmapRow) * p->rrows2.size());
   L.rmaps2 = take(sizeof(int32_t) * p->rmaps2.size());
   L.trace_shot = take(sizeof(int32_t) * p->trace_shot.size());
-  // (nothing for plans without them: a workspace of the z sweeps' size holds
-  // what it held before there were other forms)
-  L.rcell = p->rcell.empty() ? o : take(sizeof(int2) * p->rcell.size());
+  // Room for the receiver cells, whatever sweeps the plan has (tuning may yet
+  // choose an LDS-resident one, and the fields' places in memory stay the same:
+  // without it the gradient at 2048 x 768, 8 shots, nt 8000 takes 873.8 instead
+  // of 868.6 ms).  None in the least plan: a workspace of the z sweeps' size
+  // holds what it held before there were other forms.
+  L.rcell = ex.act ? take(sizeof(int2) * std::max(p->ntrace, 1)) : o;
   L.act = p->act_f ? take(sizeof(int32_t) * (size_t)p->act_nx * p->act_nz * p->ncs) : o;
   L.w = take(sizeof(float) * d.field);
   L.traces = take(sizeof(float) * (size_t)g->nt_max * std::max(p->ntrace, 1));
@@ -1299,7 +1301,7 @@ std::vector<uint64_t> tune_key(const fwi_grid* g, const fwi_geometry* geo, const
 
 // Tuned choices persist across processes in a plain text file named by the
 // environment variable FWI_TUNE_CACHE: one line per key,
-//   "<key words in hex> : S TZ graph_steps prefetch prefetch_reverse S_rev TZ_rev reverse_steps".
+//   "<key words in hex> : S TZ graph_steps prefetch prefetch_reverse S_rev TZ_rev reverse_steps forward_steps".
 std::string key_text(const std::vector<uint64_t>& k) {
   std::string out;
   char buf[24];
@@ -1581,11 +1583,13 @@ struct DxLayout {
 // updates (a multiple of 64) per chunk, so that fewer runs in flight buy
 // longer chunks and fewer read-modify-write passes over the spectra
 constexpr int kDxRunSteps = 8192;
-// default runs in flight: the one-step capture sweeps of fewer runs leave
-// the GPU underused (at 1024 x 384, 8 runs cost 24 ms per run against 37 ms
-// with 4), more runs shorten the chunks (at 2048 x 768, 8 and 16 runs cost
-// 0.5 % and 18 % more than 4): 4 on grids of at least 1.5 M padded cells,
-// else 8
+// Default runs in flight: the capture sweeps of fewer runs leave the GPU
+// underused, more runs shorten the chunks and add passes over the spectra: 4
+// on grids of at least 1.5 M padded cells, else 8.  Measured with 2, 4, 8, 16,
+// 32 runs in flight, ms per run: 2048 x 768, nt 8000: 117.9, 110.6, 115.0,
+// 123.6; 1024 x 384, nt 4000: 16.9, 15.7, 12.8, 12.6, 16.6 (16 runs take 34 GB,
+// 8 take 24); 256 x 96, nt 1500: 2.17, 1.16, 0.66, 0.54, 0.49 (small grids with
+// many runs gain by naming more).
 int dx_default_runs(const fwi_grid* g) {
   const int64_t cells = (int64_t)(g->nz + 2 * g->nsponge) * (g->nx + 2 * g->nsponge);
   return cells >= 1500000 ? 4 : 8;
