@@ -1023,13 +1023,15 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   else RSs = {1, 2};
   const bool grad = (what == FWI_WS_GRADIENT || what == FWI_WS_AUTOGRAD || what == FWI_WS_EXTIMAGE ||
                      what == FWI_WS_GNHVP);
+  const bool born = what == FWI_WS_BORN || what == FWI_WS_GNHVP;
   // forward time steps per launch: two for the gradient's forward sweep
   // (not the Born one), tried first so that near-ties keep the fewer bytes
   std::vector<int> FSs;
   if (named_forward_steps(ex, what) > 0) FSs = {ex->forward_steps};
-  else if (g->free_surface || what == FWI_WS_BORN || what == FWI_WS_GNHVP) FSs = {1};
+  else if (g->free_surface || born) FSs = {1};
   else FSs = {2, 1};
-  const int fwd_flags = grad ? (kFwdRecord | kFwdCkpt) : (what == FWI_WS_HESSIAN ? kFwdIllum : kFwdRecord);
+  const int fwd_flags = (grad ? (kFwdRecord | kFwdCkpt) : (what == FWI_WS_HESSIAN ? kFwdIllum : kFwdRecord)) |
+                        (born ? kFwdBorn : 0);
   const int nsteps = 32;  // launches timed per candidate
   // FWI_TUNE_LOG set: each candidate's best time goes to stderr
   const bool tune_log = getenv("FWI_TUNE_LOG") != nullptr;
@@ -1069,6 +1071,7 @@ int autotune(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
         p->act_f = false;  // the first steps reach few tiles: time whole launches
         if (begin_call(*p, ws, v, s) != FWI_OK) return nullptr;
         if (launch_fill(at<char>(ws, p->L.u), p->L.g - p->L.u, s) != hipSuccess) return nullptr;
+        if (born && launch_fill(at<char>(ws, p->L.bu), p->L.total - p->L.bu, s) != hipSuccess) return nullptr;
         return p;
       };
       // within one (S, TZ) a longer prefetch must win by 2 %, so near-ties
