@@ -262,14 +262,15 @@ struct Ring {
   }
 };
 
-// FP64 coefficients of the sponge by cells into it: 1 - g, 1 + g, 1 / (1 + g)
+// FP64 coefficients of the sponge by cells into it: 1 - g, 1 / (1 + g)
 struct Sponge {
-  double minus, plus, inv;
+  double minus;
+  Reciprocal plus;
 };
 __device__ __forceinline__ void sponge_table(Sponge* tab, double sp_a, int N) {
   for (int k = threadIdx.x; k <= N; k += blockDim.x) {
     const double gm = sp_a * (double)(k * k);
-    tab[k] = Sponge{1.0 - gm, 1.0 + gm, 1.0 / (1.0 + gm)};
+    tab[k] = Sponge{1.0 - gm, reciprocal(1.0 + gm)};
   }
 }
 // The damped cells of one row of a patch take ((1 - g) old + w lap) / (1 + g)
@@ -286,7 +287,7 @@ __device__ __forceinline__ void damp_row(const Sponge (&t)[4], uint32_t model, c
     x[j] = SECOND ? 2.0 * (double)c[j] - t[j].minus * (double)old[j] + (double)w[j] * (double)lap[j]
                   : t[j].minus * (double)old[j] + (double)w[j] * (double)lap[j];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) x[j] = quotient(x[j], t[j].plus, t[j].inv);
+  for (int j = 0; j < 4; ++j) x[j] = quotient(x[j], t[j].plus);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     float s = (float)x[j];

@@ -1439,8 +1439,8 @@ int get_plan(const fwi_grid* g, const fwi_geometry* geo, const fwi_exec* ex, int
   auto settle = [&](bool small) {
     c = tuned;
     // Two steps per launch by request or tuning come with an even snapshot
-    // spacing: the reconstruction's rounding (1e-5 of the gradient over 4000
-    // steps) depends on where it restarts.  Tuned calls are sized for the
+    // spacing: the reconstruction's rounding (3e-6 to 9e-5 of the gradient at
+    // 950 to 7900 steps) depends on where it restarts.  Tuned calls are sized for the
     // spacing that keeps more and the longer windows.
     c.win2 = c.rsteps == 2 && !plain && !g->free_surface;
     c.even_k = c.win2 && !(sizing_only && !compact && tuned_call);

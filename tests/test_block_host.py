@@ -18,15 +18,18 @@ static uint64_t bits(double x) { uint64_t b; std::memcpy(&b, &x, 8); return b; }
 int main() {
   const double inf = INFINITY;
   const double special[] = {inf, -inf, NAN, 0.0, -0.0, 1e-90, -1e-90, 1.1e77, -1.1e77, 1.0, -3.0};
+  const double exact[] = {1.0, 2.0, 1.5, 1.25, 4.0};
   std::mt19937_64 rng(7);
   std::normal_distribution<double> mant(0.0, 1.0);
   std::uniform_int_distribution<int> expo(-120, 120);
   int bad = 0;
   auto check = [&](double x, double plus) {
-    const double got = fwi::quotient(x, plus, 1.0 / plus), want = x / plus;
+    const double got = fwi::quotient(x, fwi::reciprocal(plus)), want = x / plus;
     if (std::isnan(want) ? !std::isnan(got) : bits(got) != bits(want))
       if (bad++ < 10) std::printf("%a / %a: %a, not %a\n", x, plus, got, want);
   };
+  for (double plus : exact)
+    for (double x : special) check(x, plus);
   // 1 + g over the depths of sponges 4 to 128 cells wide; x as the sweeps form
   // it, sums of float products
   for (int N : {4, 8, 20, 50, 128}) {
